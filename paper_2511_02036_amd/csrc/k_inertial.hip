@@ -357,21 +357,24 @@ __global__ __launch_bounds__(256) void k_vi_system(ViArgs a) {
     const WinInfo W = a.win[w], V = a.vwin[w];
     double *S = a.vred + V.red_off;
     const double *Sv = a.red + W.red_off;
-    const int n = V.n, E = V.E;
+    const int n = V.n, E = V.E, rhs = red_rhs(n, true);   // the joint system in k_chol_tile's layout
     for (int idx = tid; idx < E + n; idx += 256) {
         double v = 0.0;
+        int o;
         if (idx < E) {
             int row = (int)((sqrt(8.0 * idx + 1.0) - 1.0) * 0.5);
             while (row * (row + 1) / 2 > idx) --row;
             while ((row + 1) * (row + 2) / 2 <= idx) ++row;
             const int col = idx - row * (row + 1) / 2;
+            o = red_index(row, col);
             if (row % 15 < 6 && col % 15 < 6)
                 v = Sv[packed_lower(6 * (row / 15) + row % 15, 6 * (col / 15) + col % 15)];
         } else {
             const int i = idx - E;
+            o = rhs + i;
             if (i % 15 < 6) v = Sv[W.E + 6 * (i / 15) + i % 15];
         }
-        S[idx] = v;
+        S[o] = v;
     }
     __syncthreads();
     for (int e = a.edge_off[w]; e < a.edge_off[w + 1]; ++e) {
@@ -385,11 +388,11 @@ __global__ __launch_bounds__(256) void k_vi_system(ViArgs a) {
             const int oa = la < 15 ? oi : oj, oc = lc < 15 ? oi : oj;
             if (oa < 0 || oc < 0) continue;
             const int ga = 15 * oa + la % 15, gc = 15 * oc + lc % 15;
-            S[ga >= gc ? packed_lower(ga, gc) : packed_lower(gc, ga)] += rec[kViH + idx];
+            S[ga >= gc ? red_index(ga, gc) : red_index(gc, ga)] += rec[kViH + idx];
         }
         if (tid < 30) {
             const int o = tid < 15 ? oi : oj;
-            if (o >= 0) S[E + 15 * o + tid % 15] += rec[kViB + tid];
+            if (o >= 0) S[rhs + 15 * o + tid % 15] += rec[kViB + tid];
         }
         __syncthreads();
     }

@@ -4,8 +4,17 @@
 #include "lba_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace lba {
+
+__device__ __forceinline__ void tri_decode(int e, int &ii, int &jj) {
+    int r = (int)((sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);
+    while (r * (r + 1) / 2 > e) --r;
+    while ((r + 1) * (r + 2) / 2 <= e) ++r;
+    ii = r;
+    jj = e - r * (r + 1) / 2;
+}
 
 // ------------------------------------------------------------------------------------
 // partial sums -> reduced system.  Each block owns 64 entries of one window; its four
@@ -50,7 +59,19 @@ __global__ __launch_bounds__(256) void k_reduce(ReduceArgs a) {
     }
     acc4[g][lane] = (s0 + s1) + (s2 + s3);
     __syncthreads();
-    if (g == 0 && i < tot) a.red[W.red_off + i] = (acc4[0][lane] + acc4[1][lane]) + (acc4[2][lane] + acc4[3][lane]);
+    if (g == 0 && i < tot) {
+        int64_t o = i;
+        if (a.tiled) {
+            if (i < W.E) {
+                int row, col;
+                tri_decode(i, row, col);
+                o = red_index(row, col);
+            } else {
+                o = red_rhs(W.n, true) + (i - W.E);
+            }
+        }
+        a.red[W.red_off + o] = (acc4[0][lane] + acc4[1][lane]) + (acc4[2][lane] + acc4[3][lane]);
+    }
 }
 
 hipError_t launch_reduce(const ReduceArgs &a, int n_windows, hipStream_t s) {
@@ -62,7 +83,7 @@ hipError_t launch_reduce(const ReduceArgs &a, int n_windows, hipStream_t s) {
 
 // ------------------------------------------------------------------------------------
 // Dense FP64 Cholesky of S + lambda I and the two triangular solves for systems too large
-// for the register-tile variant below (more than 216 unknowns): one block of 512 threads
+// for the matrix-core variant below (more than 216 unknowns): one block of 512 threads
 // per window, S held as a packed lower triangle in a per-window copy in HBM, which one
 // block keeps hot in its XCD's L2 (kHbm; the template also keeps the LDS-resident form).
 // Right-looking with 8-column panels.  Per panel every thread reads the 8x8 diagonal
@@ -82,14 +103,6 @@ constexpr int kNB = LBA_CHOL_NB;
 constexpr int kCholThreads = 512;
 
 size_t chol_lds_bytes_hbm(int n) { return sizeof(double) * (4 * (size_t)n + (size_t)kNB * n) + 64; }
-
-__device__ __forceinline__ void tri_decode(int e, int &ii, int &jj) {
-    int r = (int)((sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);
-    while (r * (r + 1) / 2 > e) --r;
-    while ((r + 1) * (r + 2) / 2 <= e) ++r;
-    ii = r;
-    jj = e - r * (r + 1) / 2;
-}
 
 // factor the nbk x nbk diagonal block whose top-left entry is (c0, c0) into registers:
 // L (lower, row-major kNB x kNB) and its reciprocal diagonal; returns false on a
@@ -332,204 +345,317 @@ __global__ __launch_bounds__(kCholThreads) void k_cholesky(CholArgs a) {
 
 
 // ------------------------------------------------------------------------------------
-// The same factorisation and solves for systems of up to 216 unknowns with the matrix in
-// registers: S + lambda I is cut into 4 x 4 tiles of its lower triangle, and thread t
-// owns tiles t, t + 512 and t + 1024 (packed row-major tile order) for the whole solve,
-// so the trailing updates read only the panel from LDS and write nothing there.  Per
-// panel of four columns:
-//   1. the owner of the diagonal tile factors it (and solves the panel's entries of y),
-//      and publishes the factor;
-//   2. the owners of the tiles below it solve them against the factor (their rows of the
-//      panel, published to LDS) and subtract their share of y;
-//   3. every owner of a trailing tile subtracts the product of its two panel rows.
-// The panel and the factor are double-buffered, so two barriers per panel suffice.  The
-// back solve L^T x = y walks the panels from the last: the diagonal owner solves the
-// panel's x, then the owners of the tiles left of the diagonal subtract their share from
-// y.  Every sum is taken in a fixed order, so solves repeat bit for bit.  Rows past n are
-// an identity block with a zero right side.
+// The same factorisation and solves for systems of up to 216 unknowns, on the FP64 matrix
+// cores with the matrix in registers: S + lambda I, with the right side appended as row n
+// (so that the forward solve L y = r is part of the factorisation) and identity rows up to
+// the next multiple of 16, is cut into 16 x 16 tiles of its lower triangle.  Tile (I, J)
+// is held transposed in the accumulator layout of v_mfma_f64_16x16x4 (lane l, value v:
+// row l % 16 of I, column l / 16 + 4 v of J) by wavefront t % 8, t its place in the
+// triangle's columns.  In that layout a tile is a B operand as it stands and the A operand
+// of its transpose, so no tile is ever rearranged.  Per panel of 16 columns:
+//   1. the tiles below the diagonal are multiplied by the inverse factor of the diagonal
+//      tile and published to LDS;
+//   2. every trailing tile subtracts the product of its two panel tiles; the owner of the
+//      next diagonal tile does that one first and factors it while the others go on.
+// The diagonal tile is factored by one wavefront with a row per lane (the four rows of 16
+// lanes hold copies): its row and the identity's row, which the same column operations turn
+// into the inverse factor; a step's pivot row comes by DPP broadcasts, one reciprocal
+// square root per step is on the serial path.  The back solve L^T x = y multiplies by the stored
+// inverse factors (no serial chain within a panel), one barrier per panel.  Every sum is
+// taken in a fixed order, so solves repeat bit for bit.
+// What bounds it: the chain of diagonal tiles (update 0.4k, 16 elimination steps 2.6k of the
+// about 6k cycles per panel, panel tiles, two barriers), not the FP64 matrix rate of one
+// compute unit (n^3 / 3 flops take 9 us at n = 180).  4 x 4 tiles in registers with 4-column
+// panels took four times the barriers and panel steps.  One system, before and now: n = 120
+// 61 and 31 us, n = 180 136 and 55 us, n = 216 about 170 and 77 us.
 // ------------------------------------------------------------------------------------
-constexpr int kRegMaxN = 216;                  // 54 tile rows, 1,485 tiles <= 3 x 512
-constexpr int kRegThreads = 512;
-constexpr int kRegSlots = 3;
+constexpr int kTileMaxN = 216;
+constexpr int kTileMaxNB = (kTileMaxN + 1 + 15) / 16;               // 14 tile rows
+constexpr int kTileThreads = 512;
+constexpr int kTileWaves = kTileThreads / 64;
+constexpr int tile_slots(int nb) { return (nb * (nb + 1) / 2 + kTileWaves - 1) / kTileWaves; }   // tiles per wavefront
 
-int chol_reg_max_n() { return kRegMaxN; }
+int chol_tile_max_n() { return kTileMaxN; }
 
-__global__ __launch_bounds__(kRegThreads) void k_chol_reg(CholArgs a) {
-    __shared__ double P[2][kRegMaxN][4];   // panel rows: L[r][4k .. 4k + 3]
-    __shared__ double Lk[2][16];           // factored diagonal tile (row-major 4 x 4)
-    __shared__ double Rk[2][4];            // its reciprocal pivots
-    __shared__ double y[kRegMaxN], xs[kRegMaxN], rr[kRegMaxN], rdg[kRegMaxN];
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+template <int ror>
+__device__ __forceinline__ double row_ror(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x120 + ror, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x120 + ror, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(unsigned)lo | ((long long)hi << 32));
+}
+
+// lane c ^ 1 or c ^ 2
+template <int x>
+__device__ __forceinline__ double quad_xor(double v) {
+    constexpr int perm = x == 1 ? 0xB1 : 0x4E;   // [1, 0, 3, 2] or [2, 3, 0, 1]
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, perm, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), perm, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(unsigned)lo | ((long long)hi << 32));
+}
+
+__device__ __forceinline__ double join_fp64(unsigned lo, unsigned hi) {
+    return __longlong_as_double((long long)lo | ((long long)hi << 32));
+}
+
+// sum over the four rows of 16 lanes, in every lane
+__device__ __forceinline__ double group_sum(double v) {
+    unsigned lo = (unsigned)__double_as_longlong(v), hi = (unsigned)(__double_as_longlong(v) >> 32);
+    const auto l2 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h2 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    const double u = join_fp64(l2[0], h2[0]) + join_fp64(l2[1], h2[1]);
+    lo = (unsigned)__double_as_longlong(u);
+    hi = (unsigned)(__double_as_longlong(u) >> 32);
+    const auto l1 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), h1 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return join_fp64(l1[0], h1[0]) + join_fp64(l1[1], h1[1]);
+}
+
+// lane j of each row of 16 lanes to the whole row
+template <int j>
+__device__ __forceinline__ double row_bcast(double v) {
+    return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(v), 0x150 + j, 0xF, 0xF, true));
+}
+
+// reciprocal square root: the hardware estimate and one third-order step
+__device__ __forceinline__ double rsqrt_fp64(double p) {
+    const double y = __builtin_amdgcn_rsq(p);
+    const double e = fma(-(p * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// elimination steps j .. 15 with a row per lane of the tile (A) and of what becomes the
+// transposed inverse factor (B); columns from `real` on are padding (pivot 1)
+template <int j>
+__device__ __forceinline__ void row_steps(double (&A)[16], double (&B)[16], bool &ok, int real) {
+    double p = row_bcast<j>(A[j]);
+    if (j >= real) p = 1.0;
+    ok = ok && p > 0.0 && p < __builtin_huge_val();
+    const double rs = rsqrt_fp64(p);
+    A[j] *= rs;   // L[i][j]
+    B[j] *= rs;
+    const double v = -A[j] * rs, u = -B[j] * rs;
+#pragma unroll
+    for (int c = j + 1; c < 16; ++c) {
+        const double q = row_bcast<j>(A[c]);   // A[j][c]
+        A[c] = fma(q, v, A[c]);
+        B[c] = fma(q, u, B[c]);
+        // (B is stored by some lanes only: without this its updates would sink into that
+        // branch and keep every q alive)
+        asm volatile("" : "+v"(B[c]));
+    }
+    if constexpr (j < 15) row_steps<j + 1>(A, B, ok, real);
+}
+
+// f(constant q) for q = Q .. Q1 - 1 (constants, so that arrays indexed by them stay in
+// registers), and the same for the set bits of a uniform mask
+template <int Q, int Q1, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (Q < Q1) {
+        f(std::integral_constant<int, Q>{});
+        static_for<Q + 1, Q1>(f);
+    }
+}
+template <int Q, int Q1, typename F>
+__device__ __forceinline__ void masked_for(unsigned m, F &&f) {
+    if constexpr (Q < Q1) {
+        if ((m >> Q) & 1u) f(std::integral_constant<int, Q>{});
+        masked_for<Q + 1, Q1>(m, f);
+    }
+}
+template <int N, typename F>
+__device__ __forceinline__ void each_slot(unsigned m, F &&f) {
+    constexpr int h = N / 2;
+    if (m & ((1u << h) - 1u)) masked_for<0, h>(m, f);
+    if (m >> h) masked_for<h, N>(m, f);
+}
+#define LBA_INLINE __attribute__((always_inline))
+
+template <int kNB>   // tile rows, at most
+__global__ __launch_bounds__(kTileThreads) void k_chol_tile(CholArgs a) {
+    constexpr int kSlots = tile_slots(kNB);
+    __shared__ double Qp[kNB][4][64];   // the panel's tiles
+    __shared__ double Lt[kNB][4][64];   // inverse factors of the diagonal tiles, transposed
+    __shared__ double Ln[kNB][4][64];   // and as they are (the back solve's operand)
+    __shared__ double Dt[16][16];              // the diagonal tile being factored
+    __shared__ double y[16 * kNB], xs[16 * kNB], rr[16 * kNB];
     __shared__ int s_fail;
     const int w = blockIdx.x;
     const WinInfo W = a.win[w];
     Ctl *ctl = a.ctl + w;
     if (!ctl->running) return;
-    const int n = W.n, E = W.E;
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int n = W.n;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4;
     const double lambda = ctl->lambda;
-    const double *red = a.red + W.red_off;
-    const int NT = (n + 3) / 4, N4 = 4 * NT;
-    const int ntiles = NT * (NT + 1) / 2;
-    if (tid == 0) s_fail = (a.redflag[w] != 0.0) || n > kRegMaxN;
-    // right side (padded with zeros)
-    for (int i = tid; i < N4; i += kRegThreads) {
-        const double v = i < n ? red[E + i] : 0.0;
-        y[i] = v;
-        rr[i] = v;
-    }
-    // own tiles: loads issued for all three before any is used
-    int tI[kRegSlots], tJ[kRegSlots];
-    double T[kRegSlots][4][4];
-#pragma unroll
-    for (int u = 0; u < kRegSlots; ++u) {
-        const int t = tid + kRegThreads * u;
-        int I = -1, J = -1;
-        if (t < ntiles) tri_decode(t, I, J);
-        tI[u] = I;
-        tJ[u] = J;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int i = 4 * I + r, j = 4 * J + c;
-                double v = 0.0;
-                if (I >= 0 && i < n && j <= i) v = red[packed_lower(i, j)] + (i == j ? lambda : 0.0);
-                else if (I >= 0 && i == j) v = 1.0;   // padding rows: identity
-                T[u][r][c] = v;
+    const double *red = a.red + W.red_off, *rhs = red + red_rhs(n, true);
+    const int NB = n / 16 + 1;       // rows 0 .. n
+    const int In = n / 16, rn = n - 16 * In;   // tile row of the right side, its row there
+    const int ntiles = n < 16 * kNB ? NB * (NB + 1) / 2 : 0;
+    auto col_start = [&](int J) { return J * NB - J * (J - 1) / 2; };   // place of tile (J, J)
+    // this wavefront's slots of the places [t0, t1)
+    auto slots = [&](int t0, int t1) {
+        auto below = [&](int t) { return (1u << max(0, (t - wave + kTileWaves - 1) / kTileWaves)) - 1u; };
+        return below(t1) & ~below(t0);
+    };
+    if (tid == 0) s_fail = (a.redflag[w] != 0.0) || n >= 16 * kNB;
+    // own tiles (slot s: place wave + 8 s of the triangle's columns)
+    int tI[kSlots], tJ[kSlots];
+    d4 T[kSlots];
+    {
+        int J = 0, off = wave;       // off: place within column J
+        static_for<0, kSlots>([&](auto q) LBA_INLINE {
+            constexpr int s = q.value;
+            while (J < NB && off >= NB - J) {
+                off -= NB - J;
+                ++J;
             }
+            const bool have = wave + kTileWaves * s < ntiles;
+            tI[s] = have ? J + off : -1;
+            tJ[s] = have ? J : -1;
+            off += kTileWaves;
+            // every load is issued before any value is used (tiles that hold only the right
+            // side and padding read tile 0 instead)
+            const double *t = red + (have && 16 * tI[s] < n ? red_tile(tI[s], tJ[s]) : 0);
+            const bool diag = have && tI[s] == tJ[s];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) T[s][v] = t[diag && g + 4 * v > c ? red_in_tile(g + 4 * v, c) : 64 * v + lane];
+        });
+        for (int i = tid; i < 16 * kNB; i += kTileThreads) {
+            rr[i] = i < n ? rhs[i] : 0.0;
+            y[i] = 0.0;
+        }
+        __syncthreads();
+        static_for<0, kSlots>([&](auto q) LBA_INLINE {   // the diagonal, the right side and the padding
+            constexpr int s = q.value;
+            if (tI[s] < 0 || (tI[s] != tJ[s] && tI[s] != In)) return;
+            const int row = 16 * tI[s] + c, col0 = 16 * tJ[s] + g;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int col = col0 + 4 * v, i = min(row, col);
+                const bool side = max(row, col) == n && i < n;
+                const double b = rr[i];
+                double x = row < n && col < n ? T[s][v] : side ? b : 0.0;
+                if (row == col) x = row < n ? x + lambda : 1.0;
+                T[s][v] = x;
+            }
+        });
     }
     __syncthreads();
     // (s_fail is read only right after a barrier that follows its last write: a thread
     // that read it while another sets it would leave the panel loop alone)
     const bool failed_before = s_fail != 0;
 
+    // factor the diagonal tile D of panel k: its inverse factor goes to Lt and Ln
+    auto factor = [&](d4 D, int k) LBA_INLINE {
+        double A[16], B[16];
+        // (the lane index is re-derived behind an empty asm statement: what depends on it
+        // would otherwise be kept in registers across the panel loop, which has none left)
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        const int c = lane & 15, g = lane >> 4;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Dt[g + 4 * v][c] = D[v];
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            A[q] = Dt[q][c];   // symmetric
+            B[q] = q == c ? 1.0 : 0.0;
+        }
+        bool ok = true;
+        row_steps<0>(A, B, ok, n - 16 * k);
+        if (g == 0) {   // B: row c of the transposed inverse factor
+#pragma unroll
+            for (int q = 0; q < 16; ++q) Lt[k][c >> 2][q + 16 * (c & 3)] = B[q];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) Ln[k][q >> 2][c + 16 * (q & 3)] = B[q];
+            if (k == In && c == rn) {
+#pragma unroll
+                for (int q = 0; q < 16; ++q)
+                    if (q < rn) y[16 * k + q] = A[q];
+            }
+        }
+        if (!ok && lane == 0) s_fail = 1;
+    };
+    auto update = [&](d4 D, int I, int J) LBA_INLINE {   // D - (L_Jk) (L_Ik)^T
+        double qj[4], qi[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            qj[v] = -Qp[J][v][lane];
+            qi[v] = Qp[I][v][lane];
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) D = __builtin_amdgcn_mfma_f64_16x16x4f64(qj[v], qi[v], D, 0, 0, 0);
+        return D;
+    };
+
     // ---- factorisation and forward solve ----------------------------------------------
-    for (int k = 0; k < NT && !failed_before; ++k) {
-        const int b = k & 1;
-        // 1. the diagonal tile
+    if (!failed_before) {
+        for (int k = -1; k < NB - 1; ++k) {   // (k = -1: the first diagonal tile)
+            if (s_fail) break;
+            const int off = k < 0 ? 0 : col_start(k), nxt = k < 0 ? 0 : col_start(k + 1);
+            // 1. the tiles below the diagonal: (L_Ik)^T = L_kk^-1 (A_Ik)^T
+            each_slot<kSlots>(slots(off + 1, nxt), [&](auto q) LBA_INLINE {
+                    d4 &t = T[q.value];
+                    const int I = tI[q.value];
+                    d4 D = {0.0, 0.0, 0.0, 0.0};
+                    double li[4];
 #pragma unroll
-        for (int u = 0; u < kRegSlots; ++u) {
-            if (tI[u] != k || tJ[u] != k) continue;
-            double rd[4];
-            bool ok = true;
+                    for (int v = 0; v < 4; ++v) li[v] = Lt[k][v][lane];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                double d = T[u][c][c];
+                    for (int v = 0; v < 4; ++v) D = __builtin_amdgcn_mfma_f64_16x16x4f64(li[v], t[v], D, 0, 0, 0);
+                    t = D;
 #pragma unroll
-                for (int m = 0; m < c; ++m) d -= T[u][c][m] * T[u][c][m];
-                if (!(d > 0.0) || !isfinite(d)) ok = false;
-                const double r = rsqrt(d);
-                T[u][c][c] = d * r;
-                rd[c] = r;
+                    for (int v = 0; v < 4; ++v) Qp[I][v][lane] = D[v];
+                    if (I == In && c == rn) {
 #pragma unroll
-                for (int q = c + 1; q < 4; ++q) {
-                    double v = T[u][q][c];
-#pragma unroll
-                    for (int m = 0; m < c; ++m) v -= T[u][q][m] * T[u][c][m];
-                    T[u][q][c] = v * r;
-                }
+                        for (int v = 0; v < 4; ++v) y[16 * k + g + 4 * v] = D[v];
+                    }
+                });
+            __syncthreads();
+            // 2. trailing tiles, the next diagonal tile first
+            if ((nxt & (kTileWaves - 1)) == wave) {
+                d4 D = {0.0, 0.0, 0.0, 0.0};
+                each_slot<kSlots>(1u << (nxt / kTileWaves), [&](auto q) LBA_INLINE { D = T[q.value]; });
+                if (k >= 0) D = update(D, k + 1, k + 1);
+                factor(D, k + 1);
             }
-            double yk[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                double v = y[4 * k + c];
-#pragma unroll
-                for (int m = 0; m < c; ++m) v -= T[u][c][m] * yk[m];
-                yk[c] = v * rd[c];
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) Lk[b][4 * r + c] = c <= r ? T[u][r][c] : 0.0;
-                Rk[b][r] = rd[r];
-                rdg[4 * k + r] = rd[r];
-                y[4 * k + r] = yk[r];
-            }
-            if (!ok) s_fail = 1;
-        }
-        __syncthreads();
-        if (s_fail) break;
-        // 2. the tiles below the diagonal tile: L_Ik = A_Ik L_kk^-T
-        double lk[16], rk[4], yk[4];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) lk[q] = Lk[b][q];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            rk[c] = Rk[b][c];
-            yk[c] = y[4 * k + c];
-        }
-#pragma unroll
-        for (int u = 0; u < kRegSlots; ++u) {
-            if (tJ[u] != k || tI[u] <= k) continue;
-            const int I = tI[u];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                double dy = 0.0;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    double v = T[u][r][c];
-#pragma unroll
-                    for (int m = 0; m < c; ++m) v -= T[u][r][m] * lk[4 * c + m];
-                    T[u][r][c] = v * rk[c];
-                    P[b][4 * I + r][c] = T[u][r][c];
-                    dy += T[u][r][c] * yk[c];
-                }
-                y[4 * I + r] -= dy;   // the only writer of these rows in this panel
-            }
-        }
-        __syncthreads();
-        // 3. trailing tiles (J > k): A_IJ -= L_Ik L_Jk^T
-#pragma unroll
-        for (int u = 0; u < kRegSlots; ++u) {
-            if (tJ[u] <= k) continue;
-            const int I = tI[u], J = tJ[u];
-            double pi[4][4], pj[4][4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    pi[r][c] = P[b][4 * I + r][c];
-                    pj[r][c] = P[b][4 * J + r][c];
-                }
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    T[u][r][c] -= pi[r][0] * pj[c][0] + pi[r][1] * pj[c][1] + pi[r][2] * pj[c][2] + pi[r][3] * pj[c][3];
+            if (k >= 0)
+                each_slot<kSlots>(slots(nxt + 1, ntiles),
+                          [&](auto q) LBA_INLINE { T[q.value] = update(T[q.value], tI[q.value], tJ[q.value]); });
+            __syncthreads();
         }
     }
     __syncthreads();
     const int ok = !s_fail;
 
-    // ---- back solve L^T x = y, two barriers per panel -----------------------------------
+    // ---- back solve L^T x = y, one barrier per panel -------------------------------------
+    // x_k = L_kk^-T y_k (every wavefront forms it), then the owners of the tiles left of
+    // the diagonal subtract their share (L_kJ)^T x_k from y_J
     if (ok) {
-        for (int k = NT - 1; k >= 0; --k) {
+        for (int k = NB - 1; k >= 0; --k) {
+            double x = 0.0;
 #pragma unroll
-            for (int u = 0; u < kRegSlots; ++u) {
-                if (tI[u] != k || tJ[u] != k) continue;
-                double xk[4];
+            for (int v = 0; v < 4; ++v) x = fma(Ln[k][v][lane], y[16 * k + g + 4 * v], x);
+            x = group_sum(x);   // x_k[c]
+            if (wave == 0 && g == 0) xs[16 * k + c] = x;
+            unsigned todo = 0;
+            static_for<0, kSlots>([&](auto q) LBA_INLINE { todo |= (tI[q.value] == k && tJ[q.value] < k) ? 1u << q.value : 0u; });
+            each_slot<kSlots>(todo, [&](auto slot) LBA_INLINE {
+                    const d4 &t = T[slot.value];
+                    const int J = tJ[slot.value];
+                    double q[4];
 #pragma unroll
-                for (int c = 3; c >= 0; --c) {
-                    double v = y[4 * k + c];
-#pragma unroll
-                    for (int m = c + 1; m < 4; ++m) v -= T[u][m][c] * xk[m];
-                    xk[c] = v * rdg[4 * k + c];
-                }
-#pragma unroll
-                for (int c = 0; c < 4; ++c) xs[4 * k + c] = xk[c];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < kRegSlots; ++u) {
-                if (tI[u] != k || tJ[u] >= k) continue;
-                const int J = tJ[u];
-                double xk[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) xk[r] = xs[4 * k + r];
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    y[4 * J + c] -= T[u][0][c] * xk[0] + T[u][1][c] * xk[1] + T[u][2][c] * xk[2] + T[u][3][c] * xk[3];
-            }
+                    for (int v = 0; v < 4; ++v) q[v] = t[v] * x;
+                    // sums over the 16 lanes of a row: lane c keeps value c % 4
+                    const double u0 = (c & 1 ? q[1] : q[0]) + quad_xor<1>(c & 1 ? q[0] : q[1]);
+                    const double u1 = (c & 1 ? q[3] : q[2]) + quad_xor<1>(c & 1 ? q[2] : q[3]);
+                    double d = (c & 2 ? u1 : u0) + quad_xor<2>(c & 2 ? u0 : u1);
+                    d += row_ror<4>(d);
+                    d += row_ror<8>(d);
+                    if (c < 4) y[16 * J + g + 4 * c] -= d;
+                });
             __syncthreads();
         }
     }
@@ -554,7 +680,9 @@ size_t chol_static_lds() { return kernel_static_lds((const void *)k_cholesky<tru
 hipError_t launch_cholesky(const CholArgs &a, int n_windows, size_t lds, hipStream_t s) {
     if (n_windows <= 0) return hipSuccess;
     if (a.fact) hipLaunchKernelGGL(k_cholesky<true>, dim3(n_windows), dim3(kCholThreads), lds, s, a);
-    else hipLaunchKernelGGL(k_chol_reg, dim3(n_windows), dim3(kRegThreads), 0, s, a);
+    else if (a.max_n < 16 * 8) hipLaunchKernelGGL(k_chol_tile<8>, dim3(n_windows), dim3(kTileThreads), 0, s, a);
+    else if (a.max_n < 16 * 12) hipLaunchKernelGGL(k_chol_tile<12>, dim3(n_windows), dim3(kTileThreads), 0, s, a);
+    else hipLaunchKernelGGL(k_chol_tile<kTileMaxNB>, dim3(n_windows), dim3(kTileThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -87,6 +87,7 @@ struct Plan {
     std::vector<int32_t> order;   // launch order of the tiles: estimated heaviest first
     std::vector<int32_t> opt_map;
     std::vector<int32_t> kf_off, pt_off, obs_off;
+    int max_n = 0;           // unknowns of the largest reduced system
     size_t lin_lds = 0, upd_lds = 0, chol_lds = 0, init_lds = 0;
     bool chol_hbm = false;   // reduced systems factored in HBM (too large for LDS)
     int lin_passes = 1;      // linearisation passes over the camera blocks
@@ -256,7 +257,7 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
         W.partr_off = partr;
         partr += (int64_t)W.n * W.ntiles;
         W.red_off = (int32_t)red;
-        red += W.E + W.n;
+        red += std::max(red_rhs(W.n, true), W.E) + W.n;   // either layout
         W.dp_off = (int32_t)dpo;
         dpo += W.n;
         W.pad = 0;
@@ -336,7 +337,7 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
             V.n = 15 * pl.win[w].Kopt;
             V.E = V.n * (V.n + 1) / 2;
             V.red_off = (int32_t)vred;
-            vred += V.E + V.n;
+            vred += red_rhs(V.n, true) + V.n;
             V.dp_off = (int32_t)vdp;
             vdp += V.n;
             maxn = std::max(maxn, V.n);
@@ -344,9 +345,10 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
         if (vred > INT32_MAX) return set_error(ctx, LBA_ERR_UNSUPPORTED, "batch too large");
     }
     // the reduced system is factored in LDS when it fits, else in a per-window copy in HBM
-    // (systems of up to chol_reg_max_n() unknowns are factored with the matrix in registers
+    // (systems of up to chol_tile_max_n() unknowns are factored with the matrix in registers
     // and static LDS only; larger ones in a per-window copy in HBM)
-    pl.chol_hbm = maxn > chol_reg_max_n();
+    pl.max_n = maxn;
+    pl.chol_hbm = maxn > chol_tile_max_n();
     pl.chol_lds = pl.chol_hbm ? chol_lds_bytes_hbm(maxn) : 0;
     if (pl.chol_lds + chol_static_lds() > (size_t)ctx->max_lds || (pl.chol_hbm && pl.vi))
         return set_error(ctx, LBA_ERR_UNSUPPORTED, "reduced system of %d unknowns does not fit in LDS", maxn);
@@ -808,6 +810,7 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     ra.red = d_red;
     ra.redflag = d_redflag;
     ra.max_En = pl.max_En;
+    ra.tiled = !pl.vi && !pl.chol_hbm;
 
     CholArgs ca;
     memset(&ca, 0, sizeof(ca));
@@ -817,6 +820,7 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     ca.redflag = d_redflag;
     ca.dp = d_dp;
     ca.fact = pl.chol_hbm ? static_cast<double *>(W_(pl.o_fact)) : nullptr;
+    ca.max_n = pl.max_n;
     if (pl.vi) {   // the joint reduced system of 15 Kopt unknowns per window
         ca.win = va.vwin;
         ca.red = va.vred;

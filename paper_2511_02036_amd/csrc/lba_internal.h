@@ -36,6 +36,21 @@ struct Tile {
     int32_t win, p0, p1, pad;         // global point range [p0, p1) of one window
 };
 
+// Layout of a reduced system in memory.  Systems that k_chol_tile factors are stored as
+// 16 x 16 tiles of the lower triangle, row of tiles by row of tiles, each in the order in
+// which a wavefront holds it (value 64 v + l: row l % 16, column l / 16 + 4 v), so that a
+// tile loads as four contiguous 512-byte runs; the others as a packed lower triangle.  The
+// right side follows the matrix.
+__host__ __device__ inline int red_tile(int I, int J) { return 256 * (I * (I + 1) / 2 + J); }
+__host__ __device__ inline int red_in_tile(int r, int c) { return 64 * (c >> 2) + 16 * (c & 3) + r; }
+__host__ __device__ inline int red_index(int row, int col) {   // row >= col
+    return red_tile(row >> 4, col >> 4) + red_in_tile(row & 15, col & 15);
+}
+__host__ __device__ inline int red_rhs(int n, bool tiled) {
+    const int nb = (n + 15) / 16;
+    return tiled ? 256 * (nb * (nb + 1) / 2) : n * (n + 1) / 2;
+}
+
 // per-window Levenberg-Marquardt state, lives in device memory for the whole solve
 struct Ctl {
     double lambda, nu, F, F_trial, denom_p;
@@ -154,9 +169,10 @@ struct ReduceArgs {
     const double *part;
     const double *partr;
     const double *partd;
-    double *red;                 // per window: E packed-lower S, then n r
+    double *red;                 // per window: S, then n r (see red_rhs)
     double *redflag;             // per window fail flag
     int max_En;
+    int tiled;                   // layout of S in red: 16 x 16 tiles, else packed lower
 };
 
 struct CholArgs {
@@ -165,8 +181,9 @@ struct CholArgs {
     const double *red;
     const double *redflag;
     double *dp;
-    double *fact;   // systems too large for LDS: per window E doubles at red_off, factored in
-                    // place (nullptr: the system is factored in LDS)
+    double *fact;   // systems too large for k_chol_tile: per window E doubles at red_off,
+                    // factored in place (nullptr: every system is factored by k_chol_tile)
+    int max_n;      // unknowns of the largest system
 };
 
 struct UpdArgs {
@@ -322,7 +339,7 @@ hipError_t launch_init(const LinArgs &a, int ntiles, size_t lds, hipStream_t s);
 hipError_t launch_reduce(const ReduceArgs &a, int n_windows, hipStream_t s);
 hipError_t launch_cholesky(const CholArgs &a, int n_windows, size_t lds, hipStream_t s);
 size_t chol_lds_bytes_hbm(int n);   // LDS of the variant whose matrix is in HBM
-int chol_reg_max_n();               // largest system the register-tile variant factors
+int chol_tile_max_n();               // largest system k_chol_tile factors
 hipError_t launch_decide(const DecideArgs &a, int n_windows, hipStream_t s);
 hipError_t launch_init_reduce(const InitReduceArgs &a, int n_windows, hipStream_t s);
 hipError_t launch_setup(const MiscArgs &a, int n_windows, hipStream_t s);
