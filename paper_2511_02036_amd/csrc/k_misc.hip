@@ -72,7 +72,7 @@ __global__ void k_setup(MiscArgs a) {
         }
         a.pt_start[p] = lo;
     }
-    if (tid == 0) a.err[0] = 0;
+    if (tid < 8) a.err[tid] = 0;
 }
 
 hipError_t launch_setup(const MiscArgs &a, int n_windows, hipStream_t s) {

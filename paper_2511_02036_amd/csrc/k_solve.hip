@@ -138,6 +138,30 @@ __device__ __forceinline__ bool diag_block_factor(const double *A, int c0, int n
     return ok;
 }
 
+// the pose step (x, nullptr: none) per keyframe and the trial poses, for the segment form
+__device__ __forceinline__ void trial_poses(const CholArgs &a, int w, const double *x, int tid, int nth) {
+    if (!a.Tn) return;
+    const WinInfo V = a.vis_win[w];
+    for (int k = tid; k < V.K; k += nth) {
+        const int o = a.opt_map[V.kf0 + k];
+        double d[6], T[12];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            d[i] = x && o >= 0 ? x[a.stride * o + i] : 0.0;
+            a.dk[6 * (int64_t)(V.kf0 + k) + i] = d[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 12; ++i) T[i] = a.T[12 * (int64_t)(V.kf0 + k) + i];
+        double *Tn = a.Tn + 12 * (int64_t)(V.kf0 + k);
+        if (o >= 0) {
+            se3_left_update(d, T, Tn);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 12; ++i) Tn[i] = T[i];
+        }
+    }
+}
+
 template <bool kHbm>
 __global__ __launch_bounds__(kCholThreads) void k_cholesky(CholArgs a) {
     extern __shared__ __align__(16) double cs[];
@@ -340,6 +364,8 @@ __global__ __launch_bounds__(kCholThreads) void k_cholesky(CholArgs a) {
             ctl->solve_ok = ok;
             ctl->denom_p = den;
         }
+    } else {
+        trial_poses(a, w, ok ? xs : nullptr, tid - 64, nth - 64);
     }
 }
 
@@ -672,6 +698,8 @@ __global__ __launch_bounds__(kTileThreads) void k_chol_tile(CholArgs a) {
             ctl->solve_ok = ok;
             ctl->denom_p = den;
         }
+    } else {
+        trial_poses(a, w, ok ? xs : nullptr, tid - 64, kTileThreads - 64);
     }
 }
 
@@ -697,8 +725,16 @@ __global__ __launch_bounds__(64) void k_decide(DecideArgs a) {
     if (!ctl->running) return;
     const int lane = threadIdx.x;
     double Ft = 0.0, den = 0.0, fl = 0.0;
+    if (a.part_seg) {   // the window's segments
+        const int64_t s0 = a.seg_base[3 * (int64_t)W.rng0];
+        const int64_t s1 = a.seg_base[3 * ((int64_t)W.rng0 + (W.M + a.range_pts - 1) / a.range_pts)];
+        for (int64_t s = s0 + lane; s < s1; s += 64) {
+            Ft += a.part_seg[2 * s];
+            den += a.part_seg[2 * s + 1];
+        }
+    }
     const int64_t u0 = (int64_t)W.tile0 * a.split;   // the update's parts of this window's tiles
-    for (int t = lane; t < W.ntiles * a.split; t += 64) {
+    for (int t = lane; t < W.ntiles * a.split && !a.part_seg; t += 64) {
         Ft += a.partu[4 * (u0 + t)];
         den += a.partu[4 * (u0 + t) + 1];
         fl = fmax(fl, a.partu[4 * (u0 + t) + 2]);
@@ -762,7 +798,12 @@ __global__ __launch_bounds__(64) void k_decide(DecideArgs a) {
             double Tin[12];
 #pragma unroll
             for (int i = 0; i < 12; ++i) Tin[i] = T[i];
-            se3_left_update(dp + 6 * ok, Tin, T);
+            if (a.Tn) {
+#pragma unroll
+                for (int i = 0; i < 12; ++i) T[i] = a.Tn[12 * (int64_t)(W.kf0 + k) + i];
+            } else {
+                se3_left_update(dp + 6 * ok, Tin, T);
+            }
             if (a.vi_state) {   // velocity and biases move additively
                 const double *d = a.vi_dp + a.vi_win[w].dp_off + 15 * ok + 6;
                 double *st = a.vi_state + 9 * (int64_t)(W.kf0 + k);

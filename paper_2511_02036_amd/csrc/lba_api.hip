@@ -72,6 +72,10 @@ lba_status set_error(lba_ctx *ctx, lba_status st, const char *fmt, ...) {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+constexpr int kSegStageK = 64;     // keyframes whose poses eight wavefronts of a compute unit can stage in LDS
+constexpr int kSegTarget = 4096;   // segments a problem is cut into before they take several chunks
+constexpr int kSegWindow = 900;    // ... and a window
+
 constexpr size_t kGraphCache = 1024;
 
 struct Plan {
@@ -85,8 +89,13 @@ struct Plan {
     std::vector<WinInfo> win;
     std::vector<Tile> tiles;
     std::vector<int32_t> order;   // launch order of the tiles: estimated heaviest first
+    // segment linearisation: ranges of positions, chunks per segment, capacities
+    std::vector<Tile> ranges;
+    int range_pts = 0, seg_chunks = 1;
+    int64_t seg_cap = 0, chunk_cap = 0, rec_cap = 0;
     std::vector<int32_t> opt_map;
     std::vector<int32_t> kf_off, pt_off, obs_off;
+    int max_k = 0;           // keyframes of the largest window
     int max_n = 0;           // unknowns of the largest reduced system
     size_t lin_lds = 0, upd_lds = 0, chol_lds = 0, init_lds = 0;
     bool chol_hbm = false;   // reduced systems factored in HBM (too large for LDS)
@@ -101,7 +110,8 @@ struct Plan {
     size_t o_win, o_tiles, o_order, o_opt, o_kfoff, o_ptoff, o_obsoff, o_upload_end;
     size_t o_ptstart, o_ctl, o_T, o_X0, o_X1, o_part, o_partr, o_partd, o_partu, o_red, o_fact, o_redflag, o_dp, o_pf,
         o_pkey, o_ptmp, o_pinfo, o_skf, o_stype, o_soct, o_sz, o_smask, o_stats, o_err, o_log, o_planhead, o_planctr,
-        o_plan, total;
+        o_plan, o_ranges, o_kfmask, o_segbase, o_segs, o_chunks, o_chunkseg, o_segfail, o_Xp0,
+        o_Xp1, o_Tn, o_dk, o_partseg, o_rec, total;
     int64_t plan_cap = 0;   // words of the pool of chunk records (0: rebuilt at every step)
     int log_cap = 0;
     // stereo-inertial solve
@@ -260,7 +270,7 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
         red += std::max(red_rhs(W.n, true), W.E) + W.n;   // either layout
         W.dp_off = (int32_t)dpo;
         dpo += W.n;
-        W.pad = 0;
+        W.rng0 = 0;
         maxK = std::max(maxK, W.K);
         maxn = std::max(maxn, W.n);
         pl.max_En = std::max(pl.max_En, W.E + W.n);
@@ -288,6 +298,37 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
     pl.red_elems = std::max<int64_t>(red, 1);
     pl.dp_elems = std::max<int64_t>(dpo, 1);
 
+    // Segment form, for FP64 solves (the mixed form's FP32 sums depend on how the general
+    // form groups the products: on slowly converging windows another grouping moves points
+    // by 1e-7 to 1e-6 of the map's extent, about as far as that form is from FP64).
+    // A chunk holds at most 64 observations (about 52 in the mean).  A segment's record is 16
+    // KB, written once and read once, so fewer and longer segments save traffic; but about
+    // 2048 wavefronts are resident, and segments of uneven length leave the last of them
+    // alone.  Measured, linearisation + reduction + update per step: 48 windows of 8000
+    // points 391 us in 1,600 segments, 245 in 2,000, 223 in 4,100, 230 in 5,700; one window
+    // of 8000 points 48 us in 1,200 segments, 37 in 600.  A range of positions holds about
+    // four segments (the last one of a range is cut short).
+    if (!pl.mixed && P->n_obs > 0 && P->n_pt <= kSegMaxPoints) {
+        const int64_t chunks = P->n_obs / 52 + 1;
+        pl.seg_chunks = (int)std::min<int64_t>(kSegMaxChunks, std::max((chunks + kSegTarget - 1) / kSegTarget,
+                                                                     (chunks / nw + kSegWindow - 1) / kSegWindow));
+        const double per_pt = P->n_pt > 0 ? std::max(1.0, (double)P->n_obs / P->n_pt) : 1.0;
+        pl.range_pts = (int)std::max(64.0, std::min((double)kSegRange, 4.0 * 52.0 * pl.seg_chunks / per_pt));
+        for (int w = 0; w < nw; ++w) {
+            WinInfo &W = pl.win[w];
+            W.rng0 = (int)pl.ranges.size();
+            for (int p0 = 0; p0 < W.M; p0 += pl.range_pts)
+                pl.ranges.push_back({w, W.pt0 + p0, W.pt0 + std::min(W.M, p0 + pl.range_pts), 0});
+        }
+        const int64_t nr = (int64_t)pl.ranges.size();
+        // Few segments reach seg_chunks where their keyframes differ much: room for segments of
+        // two chunks in the mean, and for full records of every third one.  A plan that needs
+        // more takes the general form.
+        const int64_t least = std::min(pl.seg_chunks, 2), third = std::min(pl.seg_chunks, 3);
+        pl.seg_cap = 5 * chunks / (4 * least) + nr + 64;
+        pl.chunk_cap = 2 * chunks + P->n_pt / kSegPoints + 2 * nr + 64;
+        pl.rec_cap = (5 * chunks / (4 * third) + nr + 64) * seg_record(std::min(pl.max_kopt, kSegCams));
+    }
     // LDS: the update block uses four wavefronts if its staging fits, fewer otherwise
     pl.waves = 0;
     for (int wv = 4; wv >= 1; wv /= 2) {
@@ -348,6 +389,7 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
     // (systems of up to chol_tile_max_n() unknowns are factored with the matrix in registers
     // and static LDS only; larger ones in a per-window copy in HBM)
     pl.max_n = maxn;
+    pl.max_k = maxK;
     pl.chol_hbm = maxn > chol_tile_max_n();
     pl.chol_lds = pl.chol_hbm ? chol_lds_bytes_hbm(maxn) : 0;
     if (pl.chol_lds + chol_static_lds() > (size_t)ctx->max_lds || (pl.chol_hbm && pl.vi))
@@ -359,6 +401,7 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
     pl.o_win = o;    o = align256(o + sizeof(WinInfo) * nw);
     pl.o_tiles = o;  o = align256(o + sizeof(Tile) * std::max<size_t>(pl.tiles.size(), 1));
     pl.o_order = o;  o = align256(o + sizeof(int32_t) * std::max<size_t>(pl.tiles.size(), 1));
+    pl.o_ranges = o; o = align256(o + sizeof(Tile) * std::max<size_t>(pl.ranges.size(), 1));
     pl.o_opt = o;    o = align256(o + sizeof(int32_t) * std::max(P->n_kf, 1));
     pl.o_kfoff = o;  o = align256(o + sizeof(int32_t) * (nw + 1));
     pl.o_ptoff = o;  o = align256(o + sizeof(int32_t) * (nw + 1));
@@ -374,7 +417,6 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
     pl.o_T = o;       o = align256(o + sizeof(double) * 12 * std::max(P->n_kf, 1));
     pl.o_X0 = o;      o = align256(o + sizeof(double) * 3 * std::max(P->n_pt, 1));
     pl.o_X1 = o;      o = align256(o + sizeof(double) * 3 * std::max(P->n_pt, 1));
-    pl.o_part = o;    o = align256(o + sizeof(double) * pl.part_elems);
     pl.o_partr = o;   o = align256(o + sizeof(double) * pl.partr_elems);
     pl.o_partd = o;   o = align256(o + sizeof(double) * 4 * std::max<size_t>(pl.tiles.size(), 1));
     // the update splits each tile into parts of about 512 points (one block each): it
@@ -390,7 +432,7 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
     pl.o_redflag = o; o = align256(o + sizeof(double) * nw);
     pl.o_dp = o;      o = align256(o + sizeof(double) * pl.dp_elems);
     pl.o_pf = o;      o = align256(o + sizeof(double) * 12 * std::max(P->n_pt, 1));
-    pl.o_pkey = o;    o = align256(o + sizeof(uint16_t) * std::max(P->n_pt, 1));
+    pl.o_pkey = o;    o = align256(o + sizeof(uint32_t) * std::max(P->n_pt, 1));
     pl.o_ptmp = o;    o = align256(o + sizeof(int32_t) * std::max(P->n_pt, 1));
     pl.o_pinfo = o;   o = align256(o + sizeof(int4) * std::max(P->n_pt, 1));
     // the observations copied into the linearisation order
@@ -420,7 +462,23 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
     pl.plan_cap = std::min<int64_t>(pl.plan_cap, INT32_MAX - 4);   // word offsets are 32-bit
     pl.o_planhead = o; o = align256(o + sizeof(int32_t) * slots);
     pl.o_planctr = o;  o = align256(o + sizeof(unsigned long long));
-    pl.o_plan = o;     o = align256(o + sizeof(uint32_t) * (size_t)pl.plan_cap);
+    const size_t seg_pt = pl.ranges.empty() ? 1 : P->n_pt;   // (no ranges: the general form)
+    pl.o_kfmask = o;   o = align256(o + sizeof(uint64_t) * seg_pt);
+    pl.o_segbase = o;  o = align256(o + sizeof(int64_t) * 3 * (pl.ranges.size() + 1));
+    pl.o_segs = o;     o = align256(o + sizeof(Seg) * (size_t)pl.seg_cap);
+    pl.o_chunks = o;   o = align256(o + sizeof(int4) * (size_t)pl.chunk_cap);
+    pl.o_chunkseg = o; o = align256(o + sizeof(int32_t) * (size_t)pl.chunk_cap);
+    pl.o_segfail = o;  o = align256(o + sizeof(int32_t) * (size_t)pl.seg_cap);
+    pl.o_Xp0 = o;      o = align256(o + sizeof(double) * 3 * seg_pt);
+    pl.o_Xp1 = o;      o = align256(o + sizeof(double) * 3 * seg_pt);
+    pl.o_Tn = o;       o = align256(o + sizeof(double) * 12 * std::max(P->n_kf, 1));
+    pl.o_dk = o;       o = align256(o + sizeof(double) * 6 * std::max(P->n_kf, 1));
+    pl.o_partseg = o;  o = align256(o + sizeof(double) * 2 * (size_t)pl.seg_cap);
+    // a solve takes one of the two linearisations: the records of the segments share their
+    // space with the partial systems and chunk records of the general one
+    pl.o_part = pl.o_rec = o;
+    pl.o_plan = align256(pl.o_part + sizeof(double) * pl.part_elems);
+    o = align256(std::max(pl.o_plan + sizeof(uint32_t) * (size_t)pl.plan_cap, pl.o_rec + sizeof(double) * (size_t)pl.rec_cap));
     if (pl.vi) {
         pl.o_vred = o;  o = align256(o + sizeof(double) * std::max<int64_t>(vred, 1));
         pl.o_vdp = o;   o = align256(o + sizeof(double) * std::max<int64_t>(vdp, 1));
@@ -612,6 +670,7 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         memcpy(up + pl.o_tiles, pl.tiles.data(), sizeof(Tile) * pl.tiles.size());
         memcpy(up + pl.o_order, pl.order.data(), sizeof(int32_t) * pl.order.size());
     }
+    if (!pl.ranges.empty()) memcpy(up + pl.o_ranges, pl.ranges.data(), sizeof(Tile) * pl.ranges.size());
     if (P->n_kf > 0) memcpy(up + pl.o_opt, pl.opt_map.data(), sizeof(int32_t) * P->n_kf);
     memcpy(up + pl.o_kfoff, pl.kf_off.data(), sizeof(int32_t) * (nw + 1));
     memcpy(up + pl.o_ptoff, pl.pt_off.data(), sizeof(int32_t) * (nw + 1));
@@ -730,13 +789,6 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         HIPCHK(timed(ctx, LBA_KCLASS_VALIDATE, s, [&] { return launch_vi_check(va, s); }));
         HIPCHK(timed(ctx, LBA_KCLASS_SETUP, s, [&] { return launch_vi_setup(va, s); }));
     }
-    HIPCHK(hipMemcpyAsync(down, d_err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    int32_t in_err;
-    memcpy(&in_err, down, sizeof(int32_t));
-    HIPCHK(collect_timing(ctx));
-    if (in_err) return set_error(ctx, LBA_ERR_INVALID_ARGUMENT, "invalid input: %s", describe_input_error(in_err).c_str());
-
     // point order of the linearisation (the observation structure is fixed for the solve),
     // and the observations copied into it
     int4 *d_pinfo = static_cast<int4 *>(W_(pl.o_pinfo));
@@ -753,9 +805,12 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         oa.pt_start = d_ptstart;
         oa.opt_map = d_opt;
         oa.obs_kf = P->obs_kf;
-        oa.keys = static_cast<uint16_t *>(W_(pl.o_pkey));
+        oa.keys = static_cast<uint32_t *>(W_(pl.o_pkey));
+        oa.kfmask = static_cast<unsigned long long *>(W_(pl.o_kfmask));
         oa.tmp = static_cast<int32_t *>(W_(pl.o_ptmp));
         oa.pinfo = d_pinfo;
+        oa.max_cams = pl.ranges.empty() ? 0 : kSegCams;
+        oa.min_kopt = pl.mixed ? 20 : 10;
         oa.by_keyframes = 1;
         oa.n_pt = P->n_pt;
         oa.obs = ob;
@@ -764,11 +819,43 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         oa.sobs_oct = static_cast<uint8_t *>(W_(pl.o_soct));
         oa.sobs_z = W_(pl.o_sz);
         oa.smask = static_cast<uint8_t *>(W_(pl.o_smask));
-        HIPCHK(timed(ctx, LBA_KCLASS_ORDER, s, [&] {
-            hipError_t e = launch_order(oa, nw, pl.max_pts, pl.max_kopt, s);
-            return e != hipSuccess ? e : launch_order_gather(oa, false, s);
-        }));
+        oa.err = d_err;
+        HIPCHK(timed(ctx, LBA_KCLASS_ORDER, s, [&] { return launch_order(oa, nw, pl.max_pts, pl.max_kopt, s); }));
     }
+    // the segment plan
+    SegPlanArgs sa;
+    memset(&sa, 0, sizeof(sa));
+    sa.win = d_win;
+    sa.ranges = static_cast<const Tile *>(W_(pl.o_ranges));
+    sa.opt_map = d_opt;
+    sa.pinfo = d_pinfo;
+    sa.obs = ob;
+    sa.kfmask = oa.kfmask;
+    sa.base = static_cast<int64_t *>(W_(pl.o_segbase));
+    sa.segs = static_cast<Seg *>(W_(pl.o_segs));
+    sa.chunks = static_cast<int4 *>(W_(pl.o_chunks));
+    sa.chunk_seg = static_cast<int32_t *>(W_(pl.o_chunkseg));
+    sa.words = static_cast<uint32_t *>(W_(pl.o_skf));
+    sa.sz = W_(pl.o_sz);
+    sa.info = d_err;
+    sa.seg_cap = pl.seg_cap;
+    sa.chunk_cap = pl.chunk_cap;
+    sa.rec_cap = pl.rec_cap;
+    sa.n_ranges = (int32_t)pl.ranges.size();
+    sa.n_pt = P->n_pt;
+    sa.max_chunks = pl.seg_chunks;
+    sa.max_cams = kSegCams;
+    const bool acc32 = pl.mixed && opt.schur_fp32_accum;
+    bool use_seg = !pl.ranges.empty();
+    if (use_seg) HIPCHK(timed(ctx, LBA_KCLASS_ORDER, s, [&] { return launch_seg_plan(sa, s); }));
+    HIPCHK(hipMemcpyAsync(down, d_err, sizeof(int32_t) * 4, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    int32_t info[4];
+    memcpy(info, down, sizeof(info));
+    HIPCHK(collect_timing(ctx));
+    if (info[0]) return set_error(ctx, LBA_ERR_INVALID_ARGUMENT, "invalid input: %s", describe_input_error(info[0]).c_str());
+    if (info[kSegInfoGeneral]) use_seg = false;
+    if (!use_seg) HIPCHK(timed(ctx, LBA_KCLASS_ORDER, s, [&] { return launch_order_gather(oa, false, s); }));
 
     const int ntiles = (int)pl.tiles.size();
     LinArgs la;
@@ -790,7 +877,7 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     la.partd = d_partd;
     la.pf = static_cast<double *>(W_(pl.o_pf));
     la.waves = pl.waves;
-    la.acc32 = (pl.mixed && opt.schur_fp32_accum) ? 1 : 0;
+    la.acc32 = acc32 ? 1 : 0;
     la.self_copies = pl.lin_copies;
     if (pl.plan_cap > 0) {
         la.plan = static_cast<uint32_t *>(W_(pl.o_plan));
@@ -812,6 +899,66 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     ra.max_En = pl.max_En;
     ra.tiled = !pl.vi && !pl.chol_hbm;
 
+    LinSegArgs lsa;
+    memset(&lsa, 0, sizeof(lsa));
+    lsa.win = d_win;
+    lsa.segs = sa.segs;
+    lsa.chunks = sa.chunks;
+    lsa.pinfo = d_pinfo;
+    lsa.words = sa.words;
+    lsa.sz = sa.sz;
+    lsa.T = d_T;
+    lsa.X0 = static_cast<const double *>(W_(pl.o_Xp0));
+    lsa.X1 = static_cast<const double *>(W_(pl.o_Xp1));
+    lsa.ctl = d_ctl;
+    lsa.pf = la.pf;
+    lsa.rec = static_cast<double *>(W_(pl.o_rec));
+    lsa.segfail = static_cast<int32_t *>(W_(pl.o_segfail));
+    lsa.info = d_err;
+    lsa.n_obs = P->n_obs;
+    lsa.n_pt = P->n_pt;
+    lsa.stage_k = pl.max_k <= kSegStageK ? pl.max_k : 0;
+    lsa.c = c;
+
+    UpdSegArgs usa;
+    memset(&usa, 0, sizeof(usa));
+    usa.win = d_win;
+    usa.segs = sa.segs;
+    usa.chunks = sa.chunks;
+    usa.pinfo = d_pinfo;
+    usa.words = sa.words;
+    usa.sz = sa.sz;
+    usa.T = d_T;
+    usa.Tn = static_cast<double *>(W_(pl.o_Tn));
+    usa.dk = static_cast<double *>(W_(pl.o_dk));
+    usa.X0 = static_cast<double *>(W_(pl.o_Xp0));
+    usa.X1 = static_cast<double *>(W_(pl.o_Xp1));
+    usa.ctl = d_ctl;
+    usa.pf = la.pf;
+    usa.partu = static_cast<double *>(W_(pl.o_partseg));
+    usa.info = d_err;
+    usa.n_obs = P->n_obs;
+    usa.n_pt = P->n_pt;
+    usa.max_k = pl.max_k;
+    usa.c = c;
+    const int upd_waves = std::min(4, pl.seg_chunks);
+
+    ReduceSegArgs rsa;
+    memset(&rsa, 0, sizeof(rsa));
+    rsa.win = d_win;
+    rsa.ctl = d_ctl;
+    rsa.segs = sa.segs;
+    rsa.base = sa.base;
+    rsa.rec = lsa.rec;
+    rsa.segfail = lsa.segfail;
+    rsa.red = d_red;
+    rsa.redflag = d_redflag;
+    rsa.tiled = ra.tiled;
+    rsa.range_pts = pl.range_pts;
+    rsa.max_kopt = pl.max_kopt;
+    // about 16 segments per wavefront of a camera block
+    rsa.waves = (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, P->n_obs / 52 / std::min(pl.seg_chunks, 16) / nw / 16));
+
     CholArgs ca;
     memset(&ca, 0, sizeof(ca));
     ca.win = d_win;
@@ -821,6 +968,14 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     ca.dp = d_dp;
     ca.fact = pl.chol_hbm ? static_cast<double *>(W_(pl.o_fact)) : nullptr;
     ca.max_n = pl.max_n;
+    if (use_seg) {
+        ca.vis_win = d_win;
+        ca.opt_map = d_opt;
+        ca.T = d_T;
+        ca.Tn = static_cast<double *>(W_(pl.o_Tn));
+        ca.dk = static_cast<double *>(W_(pl.o_dk));
+        ca.stride = pl.vi ? 15 : 6;
+    }
     if (pl.vi) {   // the joint reduced system of 15 Kopt unknowns per window
         ca.win = va.vwin;
         ca.red = va.vred;
@@ -858,6 +1013,12 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     da.log_cap = pl.log_cap;
     da.split = pl.upd_split;
     da.c = c;
+    if (use_seg) {
+        da.part_seg = usa.partu;
+        da.seg_base = sa.base;
+        da.Tn = usa.Tn;
+        da.range_pts = pl.range_pts;
+    }
     if (pl.vi) {
         da.vi_ed = va.ed;
         da.vi_edge_off = va.edge_off;
@@ -881,6 +1042,13 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         ia.opt_map = va.opt_map;
     }
 
+    if (use_seg) {
+        // the points live by position; the kernels that walk them in index order (damping
+        // initialisation, flags, output) read a copy brought up to date before each use
+        HIPCHK(launch_to_positions(d_pinfo, d_X0, usa.X0, P->n_pt, s));
+        la.X1 = d_X0;
+        m.X1 = d_X0;
+    }
     std::vector<Ctl> hctl(nw);
     for (int round = 1; round <= 2; ++round) {
         const int iters = round == 1 ? opt.iters_round1 : opt.iters_round2;
@@ -888,9 +1056,12 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         if (round == 2) {
             m.count = 0;
             oa.mask = R->outlier;
+            if (use_seg) HIPCHK(launch_from_positions(usa, d_X0, nw, pl.max_pts, s));
             HIPCHK(timed(ctx, LBA_KCLASS_FLAGS, s, [&] {
                 hipError_t e = launch_flags(m, nw, pl.max_obs, s);
-                return e != hipSuccess ? e : launch_order_gather(oa, true, s);   // the flags in places
+                if (e != hipSuccess) return e;
+                sa.mask = R->outlier;
+                return use_seg ? launch_seg_mask(sa, s) : launch_order_gather(oa, true, s);   // the flags in places
             }));
             mask = R->outlier;
         }
@@ -898,13 +1069,15 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         la.mask = mask;
         la.smask = mask ? oa.smask : nullptr;
         la.robust = robust;
+        lsa.robust = robust;
+        usa.robust = robust;
         ua.mask = mask;
         ua.robust = robust;
         da.round = round;
         ia.round = round;
         // the active observations change between rounds: the chunk records are formed again
         HIPCHK(timed(ctx, LBA_KCLASS_LINEARIZE_INIT, s, [&] {
-            hipError_t e = launch_plan_reset(la, ntiles * std::max(pl.lin_passes, 1), s);
+            hipError_t e = use_seg ? hipSuccess : launch_plan_reset(la, ntiles * std::max(pl.lin_passes, 1), s);
             return e != hipSuccess ? e : launch_init(la, ntiles, pl.init_lds, s);
         }));
         if (pl.vi) HIPCHK(timed(ctx, LBA_KCLASS_INERTIAL, s, [&] { return launch_vi_eval(va, s); }));
@@ -915,10 +1088,14 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         // one LM step over every window: [linearise, reduce, factor + solve, update, decide]
         auto step = [&](hipStream_t q) -> hipError_t {
             hipError_t e;
-            if ((e = timed(ctx, LBA_KCLASS_LINEARIZE, q,
-                           [&] { return launch_linearize(la, ntiles, pl.lin_passes, pl.lin_lds, pl.mixed, q); })) != hipSuccess)
+            if ((e = timed(ctx, LBA_KCLASS_LINEARIZE, q, [&] {
+                     return use_seg ? launch_linseg(lsa, pl.seg_cap, ob.z_f32 != 0, q)
+                                    : launch_linearize(la, ntiles, pl.lin_passes, pl.lin_lds, pl.mixed, q);
+                 })) != hipSuccess)
                 return e;
-            if ((e = timed(ctx, LBA_KCLASS_REDUCE, q, [&] { return launch_reduce(ra, nw, q); })) != hipSuccess) return e;
+            if ((e = timed(ctx, LBA_KCLASS_REDUCE, q,
+                           [&] { return use_seg ? launch_reduce_seg(rsa, nw, q) : launch_reduce(ra, nw, q); })) != hipSuccess)
+                return e;
             if (pl.vi) {
                 if ((e = timed(ctx, LBA_KCLASS_INERTIAL, q, [&] { return launch_vi_eval(va, q); })) != hipSuccess) return e;
                 if ((e = timed(ctx, LBA_KCLASS_INERTIAL, q, [&] { return launch_vi_system(va, nw, q); })) != hipSuccess)
@@ -930,7 +1107,10 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
             if (pl.vi && (e = timed(ctx, LBA_KCLASS_INERTIAL, q, [&] { return launch_vi_split(va, nw, q); })) != hipSuccess)
                 return e;
             if ((e = timed(ctx, LBA_KCLASS_UPDATE, q,
-                           [&] { return launch_update(ua, ntiles, pl.upd_lds, pl.mixed, q); })) != hipSuccess)
+                           [&] {
+                               return use_seg ? launch_updseg(usa, pl.seg_cap, upd_waves, ob.z_f32 != 0, q)
+                                              : launch_update(ua, ntiles, pl.upd_lds, pl.mixed, q);
+                           })) != hipSuccess)
                 return e;
             if (pl.vi && (e = timed(ctx, LBA_KCLASS_INERTIAL, q, [&] { return launch_vi_eval(va_trial, q); })) !=
                              hipSuccess)
@@ -941,14 +1121,20 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         if (opt.use_graphs && !ctx->prof && iters > 0) {
             std::string key;
             auto add = [&](const void *p, size_t n) { key.append(static_cast<const char *>(p), n); };
-            add(&la, sizeof(la));
-            add(&ra, sizeof(ra));
+            if (use_seg) {
+                add(&lsa, sizeof(lsa));
+                add(&rsa, sizeof(rsa));
+                add(&usa, sizeof(usa));
+            } else {
+                add(&la, sizeof(la));
+                add(&ra, sizeof(ra));
+            }
             add(&ca, sizeof(ca));
             add(&ua, sizeof(ua));
             add(&da, sizeof(da));
             add(&va, sizeof(va));
-            const int64_t dims[6] = {ntiles, nw, (int64_t)pl.lin_lds, (int64_t)pl.chol_lds, (int64_t)pl.upd_lds,
-                                     pl.mixed ? 1 : 0};
+            const int64_t dims[8] = {ntiles, nw, (int64_t)pl.lin_lds, (int64_t)pl.chol_lds, (int64_t)pl.upd_lds,
+                                     pl.mixed ? 1 : 0, use_seg ? pl.seg_cap : 0, ob.z_f32};
             add(dims, sizeof(dims));
             st = step_graph(ctx, key, step, &exec);
             if (st != LBA_OK) return st;
@@ -969,6 +1155,7 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         }
     }
     m.count = 1;
+    if (use_seg) HIPCHK(launch_from_positions(usa, d_X0, nw, pl.max_pts, s));
     HIPCHK(timed(ctx, LBA_KCLASS_FLAGS, s, [&] { return launch_flags(m, nw, pl.max_obs, s); }));
     HIPCHK(timed(ctx, LBA_KCLASS_FINALIZE, s, [&] { return launch_finalize(m, nw, s); }));
     if (pl.vi) HIPCHK(timed(ctx, LBA_KCLASS_FINALIZE, s, [&] { return launch_vi_finish(va, s); }));

@@ -26,7 +26,7 @@ struct WinInfo {
     int32_t tile0, ntiles;            // tiles of this window in the tile list
     int32_t red_off;                  // doubles: reduced system (E + n) of this window
     int32_t dp_off;                   // doubles: pose step (n) of this window
-    int32_t pad;
+    int32_t rng0;                     // first of its ranges of positions (segment plan)
     int64_t part_off;                 // doubles: partial S (E per tile) of tile 0
     int64_t part_stride;              // doubles per tile: E
     int64_t partr_off;                // doubles: partial r (n per tile) of tile 0
@@ -130,16 +130,35 @@ struct LinArgs {
     SolveConsts c;
 };
 
+// segment linearisation (k_segments, k_linseg)
+constexpr int kSegCams = 10;       // optimisable keyframes of a segment: 60 rows, four 16-row tiles
+                                   // (a fifth one would not fit in registers)
+constexpr int kSegPoints = 32;     // points of a chunk
+constexpr int kSegMaxChunks = 16;  // chunks of a segment
+constexpr int kSegRange = 512;     // positions of a range, at most
+constexpr int kSegMaxPoints = 0x7fffffff / 8;   // points of a batch: a plane of their factors is one 2 GiB buffer
+static_assert(kMaxKf <= 128, "a word holds 7 bits of keyframe");
+constexpr int kSegNoCam = 15;      // camera place of an observation on a fixed keyframe
+constexpr uint32_t kSegInactive = 1u << 23;   // word of an observation left out in round 2
+// a.info: 0 input checks, then
+constexpr int kSegInfoGeneral = 2;   // the general linearisation is needed
+constexpr int kSegInfoCount = 3;     // segments
+constexpr int kSegInfoChunks = 4;    // chunks
+
 // point order of the linearisation (k_order)
 struct OrderArgs {
     const WinInfo *win;
     const int32_t *pt_start;     // global point -> first global observation (n_pt + 1)
     const int32_t *opt_map;      // global kf -> window-local optimisable index or -1
     const int32_t *obs_kf;       // window-local keyframe of each observation
-    uint16_t *keys;              // per point: lowest | highest << 5 optimisable keyframe (n_pt)
-    int32_t *tmp;                // per window, window-local order after the first pass (n_pt)
+    uint32_t *keys;              // per point: lowest | highest << 6 optimisable keyframe |
+                                 // observations << 12 (n_pt)
+    unsigned long long *kfmask;  // per point: the set of its optimisable keyframes (n_pt)
+    int32_t *tmp;                // window-local points, grouped by lowest keyframe (n_pt)
     int4 *pinfo;                 // result, per position of the order: point, first observation,
                                  // observation count, place of the first observation (n_pt)
+    int max_cams;                // optimisable keyframes of a segment (0: no segment plan follows)
+    int min_kopt;                // windows with more optimisable keyframes are sorted
     int by_keyframes;            // 1: sort the windows with many optimisable keyframes by
                                  // keyframes; 0: index order everywhere
     int32_t n_pt;
@@ -148,8 +167,96 @@ struct OrderArgs {
     int32_t *sobs_kf;            // n_obs
     uint8_t *sobs_type, *sobs_oct;
     void *sobs_z;                // 3 x n_obs planar, the type of obs.z
+    int32_t *err;                // [0] nonzero: the input checks failed, nothing is ordered;
+                                 // [kSegInfoGeneral] is set where a point or a repeated
+                                 // observation does not suit the segments
     const uint8_t *mask;         // k_order_gather_mask: outlier flags in index order ...
     uint8_t *smask;              // ... and in places
+};
+
+struct Seg {
+    int32_t win, chunk0, nchunk, ncam;
+    unsigned long long mask;   // its optimisable keyframes
+    int64_t rec;               // doubles: its record in the pool
+    int32_t kf0, K;            // the window's keyframes
+    int4 first;                // its first chunk
+};
+
+// row tiles of a segment over u cameras, and the doubles of its record: the 6 x 6 blocks of
+// the lower block triangle, then per camera Hpp (21, lower) and r (6)
+__host__ __device__ inline int seg_row_tiles(int u) { return (6 * u + 15) / 16; }
+__host__ __device__ inline int seg_blocks(int u) { return 36 * (u * (u + 1) / 2); }
+__host__ __device__ inline int seg_record(int u) { return seg_blocks(u) + 27 * u; }
+
+struct SegPlanArgs {
+    const WinInfo *win;
+    const Tile *ranges;          // ranges of positions, each planned by one wavefront
+    const int32_t *opt_map;
+    const int4 *pinfo;           // linearisation order (see LinArgs)
+    ObsView obs;                 // index order
+    const uint8_t *mask;         // k_seg_mask: outlier flags in index order
+    const unsigned long long *kfmask;   // per point: its optimisable keyframes
+    int64_t *base;               // per range: counts, then bases, of segments, chunks, record doubles
+    Seg *segs;
+    int4 *chunks;                // first position, points, first place, observations | cameras << 8
+    int32_t *chunk_seg;          // segment of each chunk
+    uint32_t *words;             // per place (see k_seg_emit)
+    void *sz;                    // measurements by place, the type of obs.z
+    int32_t *info;
+    int64_t seg_cap, chunk_cap, rec_cap;
+    int32_t n_ranges, n_pt, max_chunks, max_cams;
+};
+
+struct LinSegArgs {
+    const WinInfo *win;
+    const Seg *segs;
+    const int4 *chunks;
+    const int4 *pinfo;
+    const uint32_t *words;
+    const void *sz;              // planar u / v / uR by place, stride n_obs
+    const double *T;             // working poses
+    const double *X0, *X1;       // points by position, double buffer
+    const Ctl *ctl;
+    double *pf;                  // by position, 9 planes of n_pt: L^-1 of V (6), t = L^-1 bl (3)
+    double *rec;                 // records of the segments
+    int32_t *segfail;            // per segment: a point block did not factorise
+    const int32_t *info;
+    int32_t n_obs, n_pt, robust;
+    int32_t stage_k;            // poses a wavefront stages in LDS (0: read from memory)
+    SolveConsts c;
+};
+
+struct UpdSegArgs {
+    const WinInfo *win;
+    const Seg *segs;
+    const int4 *chunks;
+    const int4 *pinfo;
+    const uint32_t *words;
+    const void *sz;
+    const double *T, *Tn;        // current and trial poses
+    const double *dk;            // pose step per keyframe (zero for fixed ones)
+    double *X0, *X1;             // points by position, double buffer
+    const Ctl *ctl;
+    const double *pf;            // point factors by position: 9 planes of n_pt
+    double *partu;               // per segment: trial cost, denominator part
+    const int32_t *info;
+    int32_t n_obs, n_pt, robust, max_k;
+    SolveConsts c;
+};
+
+struct ReduceSegArgs {
+    const WinInfo *win;
+    const Ctl *ctl;
+    const Seg *segs;
+    const int64_t *base;         // per range (see SegPlanArgs): first segment
+    const double *rec;
+    const int32_t *segfail;
+    double *red;
+    double *redflag;
+    int32_t tiled;               // layout of red (see ReduceArgs)
+    int32_t range_pts;           // positions per range
+    int32_t max_kopt;
+    int32_t waves;               // wavefronts per camera block
 };
 
 // stereo-inertial measurements (device view of lba_inertial)
@@ -184,6 +291,12 @@ struct CholArgs {
     double *fact;   // systems too large for k_chol_tile: per window E doubles at red_off,
                     // factored in place (nullptr: every system is factored by k_chol_tile)
     int max_n;      // unknowns of the largest system
+    // segment form (null otherwise): trial poses and pose steps per keyframe
+    const WinInfo *vis_win;      // the visual windows (win describes the joint ones in an inertial solve)
+    const int32_t *opt_map;
+    const double *T;
+    double *Tn, *dk;
+    int stride;                  // unknowns per keyframe in dp: 6, or 15 in an inertial solve
 };
 
 struct UpdArgs {
@@ -218,6 +331,12 @@ struct DecideArgs {
     int split;
     int round;                   // 1 or 2
     SolveConsts c;
+    // segment form (null otherwise): per segment trial cost and denominator part, the
+    // windows' segments, and the trial poses that an accepted step takes
+    const double *part_seg;
+    const int64_t *seg_base;
+    const double *Tn;
+    int32_t range_pts, pad;
     // stereo-inertial solve (null otherwise)
     const double *vi_ed;         // measurement records: trial costs
     const int32_t *vi_edge_off;
@@ -332,6 +451,13 @@ hipError_t launch_vi_split(const ViArgs &a, int n_windows, hipStream_t s);
 hipError_t launch_vi_finish(const ViArgs &a, hipStream_t s);
 
 hipError_t launch_linearize(const LinArgs &a, int ntiles, int passes, size_t lds, bool mixed, hipStream_t s);
+hipError_t launch_seg_plan(const SegPlanArgs &a, hipStream_t s);
+hipError_t launch_seg_mask(const SegPlanArgs &a, hipStream_t s);
+hipError_t launch_linseg(const LinSegArgs &a, int64_t seg_cap, bool z_f32, hipStream_t s);
+hipError_t launch_updseg(const UpdSegArgs &a, int64_t seg_cap, int waves, bool z_f32, hipStream_t s);
+hipError_t launch_to_positions(const int4 *pinfo, const double *X, double *Xp, int n, hipStream_t s);
+hipError_t launch_from_positions(const UpdSegArgs &a, double *X, int n_windows, int max_points, hipStream_t s);
+hipError_t launch_reduce_seg(const ReduceSegArgs &a, int n_windows, hipStream_t s);
 hipError_t launch_plan_reset(const LinArgs &a, int slots, hipStream_t s);   // forget the chunk records
 int lin_passes(int kopt);   // passes over the camera blocks of a window with kopt optimisable keyframes
 hipError_t launch_update(const UpdArgs &a, int ntiles, size_t lds, bool mixed, hipStream_t s);
