@@ -10,12 +10,9 @@
 //                Newton blocks J^T Info J (packed lower 30 x 30) and -J^T Info r, written
 //                to the measurement's record; in trial mode only the cost at the trial
 //                state (pose Exp(dp) T, velocity and biases plus the step);
-//   k_vi_system  one block per window: the joint reduced system of 15 Kopt unknowns, the
-//                visual reduced system in the pose rows and columns plus every measurement
-//                of the window added in measurement order (a fixed order: results do not
-//                depend on scheduling);
-//   k_vi_split   the pose part of the joint step in the visual step's layout, for the
-//                back-substitution and the trial poses;
+//   k_vi_system  the joint reduced system of 15 Kopt unknowns, the visual reduced system in
+//                the pose rows and columns plus the measurements of the window added in
+//                measurement order (a fixed order: results do not depend on scheduling);
 //   k_vi_setup / k_vi_finish / k_vi_check   state copies and input validation.
 // The damping decision adds the measurements' trial costs and applies the velocity and
 // bias steps (k_decide); the round's first damping includes their diagonal
@@ -350,60 +347,63 @@ __global__ __launch_bounds__(64) void k_vi_eval(ViArgs a) {
     }
 }
 
-// ---- per window: the joint reduced system ---------------------------------------------------
-__global__ __launch_bounds__(256) void k_vi_system(ViArgs a) {
-    const int w = blockIdx.x, tid = threadIdx.x;
-    if (!a.ctl[w].running) return;
-    const WinInfo W = a.win[w], V = a.vwin[w];
-    double *S = a.vred + V.red_off;
-    const double *Sv = a.red + W.red_off;
-    const int n = V.n, E = V.E, rhs = red_rhs(n, true);   // the joint system in k_chol_tile's layout
-    for (int idx = tid; idx < E + n; idx += 256) {
-        double v = 0.0;
-        int o;
-        if (idx < E) {
-            int row = (int)((sqrt(8.0 * idx + 1.0) - 1.0) * 0.5);
-            while (row * (row + 1) / 2 > idx) --row;
-            while ((row + 1) * (row + 2) / 2 <= idx) ++row;
-            const int col = idx - row * (row + 1) / 2;
-            o = red_index(row, col);
-            if (row % 15 < 6 && col % 15 < 6)
-                v = Sv[packed_lower(6 * (row / 15) + row % 15, 6 * (col / 15) + col % 15)];
-        } else {
-            const int i = idx - E;
-            o = rhs + i;
-            if (i % 15 < 6) v = Sv[W.E + 6 * (i / 15) + i % 15];
-        }
-        S[o] = v;
-    }
-    __syncthreads();
-    for (int e = a.edge_off[w]; e < a.edge_off[w + 1]; ++e) {
-        const int oi = a.opt_map[W.kf0 + a.E.ei[e]], oj = a.opt_map[W.kf0 + a.E.ej[e]];
-        const double *rec = a.ed + (int64_t)e * kViEdgeStride;
-        for (int idx = tid; idx < 465; idx += 256) {
-            int la = (int)((sqrt(8.0 * idx + 1.0) - 1.0) * 0.5);
-            while (la * (la + 1) / 2 > idx) --la;
-            while ((la + 1) * (la + 2) / 2 <= idx) ++la;
-            const int lc = idx - la * (la + 1) / 2;
-            const int oa = la < 15 ? oi : oj, oc = lc < 15 ? oi : oj;
-            if (oa < 0 || oc < 0) continue;
-            const int ga = 15 * oa + la % 15, gc = 15 * oc + lc % 15;
-            S[ga >= gc ? red_index(ga, gc) : red_index(gc, ga)] += rec[kViH + idx];
-        }
-        if (tid < 30) {
-            const int o = tid < 15 ? oi : oj;
-            if (o >= 0) S[rhs + 15 * o + tid % 15] += rec[kViB + tid];
-        }
-        __syncthreads();
-    }
-}
+// ---- the joint reduced system ---------------------------------------------------------------
+// One thread per entry: the visual system's entry, then the measurements that hold it, in
+// measurement order.  One block per window that added the measurements one after the other
+// was bound by that chain (38 us for one window of 10 optimisable keyframes and 14
+// measurements, 44 for 64 windows); an entry belongs to few measurements, whose endpoints
+// the block stages in LDS (6 and 11 us).
+constexpr int kViSysEdges = 256;   // measurements staged at a time
 
-__global__ __launch_bounds__(64) void k_vi_split(ViArgs a) {
-    const int w = blockIdx.x;
+__global__ __launch_bounds__(256) void k_vi_system(ViArgs a) {
+    __shared__ int ends[kViSysEdges];   // optimisable indices of both keyframes, 255 for none
+    const int w = blockIdx.y, tid = threadIdx.x;
     if (!a.ctl[w].running) return;
     const WinInfo W = a.win[w], V = a.vwin[w];
-    for (int i = threadIdx.x; i < V.n; i += 64)
-        if (i % 15 < 6) a.dpv[W.dp_off + 6 * (i / 15) + i % 15] = a.vdp[V.dp_off + i];
+    const int n = V.n, E = V.E, idx = blockIdx.x * 256 + tid;
+    if ((int)blockIdx.x * 256 >= E + n) return;   // (uniform)
+    const double *Sv = a.red + W.red_off;
+    const bool live = idx < E + n, side = idx >= E;
+    int row = 0, col = 0;
+    double v = 0.0;
+    if (side) {
+        row = live ? idx - E : 0;
+        if (live && row % 15 < 6) v = Sv[W.E + 6 * (row / 15) + row % 15];
+    } else {
+        row = (int)((sqrtf(8.0f * idx + 1.0f) - 1.0f) * 0.5f);
+        while (row * (row + 1) / 2 > idx) --row;
+        while ((row + 1) * (row + 2) / 2 <= idx) ++row;
+        col = idx - row * (row + 1) / 2;
+        if (row % 15 < 6 && col % 15 < 6) v = Sv[packed_lower(6 * (row / 15) + row % 15, 6 * (col / 15) + col % 15)];
+    }
+    const int A = row / 15, B = col / 15, ra = row - 15 * A, cb = col - 15 * B;
+    const int e0 = a.edge_off[w], e1 = a.edge_off[w + 1];
+    for (int eb = e0; eb < e1; eb += kViSysEdges) {
+        const int ne = min(kViSysEdges, e1 - eb);
+        __syncthreads();
+        for (int q = tid; q < ne; q += 256)
+            ends[q] = (a.opt_map[W.kf0 + a.E.ei[eb + q]] & 255) | ((a.opt_map[W.kf0 + a.E.ej[eb + q]] & 255) << 8);
+        __syncthreads();
+        if (!live) continue;
+        for (int q = 0; q < ne; ++q) {
+            const int oi = ends[q] & 255, oj = ends[q] >> 8;   // (distinct keyframes)
+            int at = -1;   // the entry's place in the measurement's record
+            if (side) {
+                if (oi == A || oj == A) at = kViB + (oj == A ? 15 : 0) + ra;
+            } else if (A == B) {
+                if (oi == A || oj == A) {
+                    const int s = oj == A ? 15 : 0;
+                    at = kViH + (s + ra) * (s + ra + 1) / 2 + s + cb;
+                }
+            } else if ((oi == A && oj == B) || (oi == B && oj == A)) {
+                const int hi = oj == A ? 15 + ra : 15 + cb, lo = oj == A ? cb : ra;
+                at = kViH + hi * (hi + 1) / 2 + lo;
+            }
+            if (at >= 0) v += a.ed[(int64_t)(eb + q) * kViEdgeStride + at];
+        }
+    }
+    // in k_chol_tile's layout
+    if (live) a.vred[V.red_off + (side ? red_rhs(n, true) + row : red_index(row, col))] = v;
 }
 
 __global__ __launch_bounds__(256) void k_vi_setup(ViArgs a) {
@@ -473,13 +473,10 @@ hipError_t launch_vi_eval(const ViArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_vi_system(const ViArgs &a, int n_windows, hipStream_t s) {
-    if (n_windows > 0) hipLaunchKernelGGL(k_vi_system, dim3(n_windows), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_vi_split(const ViArgs &a, int n_windows, hipStream_t s) {
-    if (n_windows > 0) hipLaunchKernelGGL(k_vi_split, dim3(n_windows), dim3(64), 0, s, a);
+hipError_t launch_vi_system(const ViArgs &a, int n_windows, int max_n, hipStream_t s) {
+    const int items = max_n * (max_n + 1) / 2 + max_n;
+    if (n_windows > 0 && items > 0)
+        hipLaunchKernelGGL(k_vi_system, dim3((items + 255) / 256, n_windows), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

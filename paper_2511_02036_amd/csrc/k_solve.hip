@@ -138,10 +138,14 @@ __device__ __forceinline__ bool diag_block_factor(const double *A, int c0, int n
     return ok;
 }
 
-// the pose step (x, nullptr: none) per keyframe and the trial poses, for the segment form
+// from the step x (nullptr: none): its pose part in an inertial solve; the pose step per
+// keyframe and the trial poses in the segment form
 __device__ __forceinline__ void trial_poses(const CholArgs &a, int w, const double *x, int tid, int nth) {
-    if (!a.Tn) return;
+    if (!a.Tn && !a.dpv) return;
     const WinInfo V = a.vis_win[w];
+    if (a.dpv)
+        for (int i = tid; i < V.n; i += nth) a.dpv[V.dp_off + i] = x ? x[15 * (i / 6) + i % 6] : 0.0;
+    if (!a.Tn) return;
     for (int k = tid; k < V.K; k += nth) {
         const int o = a.opt_map[V.kf0 + k];
         double d[6], T[12];

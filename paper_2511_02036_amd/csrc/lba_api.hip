@@ -770,7 +770,6 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         va.bg_out = bg_out;
         va.ba_out = ba_out;
         va.dp = d_dp;
-        va.dpv = d_dp;
         va.vdp = static_cast<double *>(W_(pl.o_vdp));
         va.red = d_red;
         va.vred = static_cast<double *>(W_(pl.o_vred));
@@ -980,6 +979,8 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         ca.win = va.vwin;
         ca.red = va.vred;
         ca.dp = static_cast<double *>(W_(pl.o_vdp));
+        ca.vis_win = d_win;
+        ca.dpv = d_dp;
     }
 
     UpdArgs ua;
@@ -1098,13 +1099,11 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
                 return e;
             if (pl.vi) {
                 if ((e = timed(ctx, LBA_KCLASS_INERTIAL, q, [&] { return launch_vi_eval(va, q); })) != hipSuccess) return e;
-                if ((e = timed(ctx, LBA_KCLASS_INERTIAL, q, [&] { return launch_vi_system(va, nw, q); })) != hipSuccess)
+                if ((e = timed(ctx, LBA_KCLASS_INERTIAL, q, [&] { return launch_vi_system(va, nw, pl.max_n, q); })) != hipSuccess)
                     return e;
             }
             if ((e = timed(ctx, LBA_KCLASS_CHOLESKY, q, [&] { return launch_cholesky(ca, nw, pl.chol_lds, q); })) !=
                 hipSuccess)
-                return e;
-            if (pl.vi && (e = timed(ctx, LBA_KCLASS_INERTIAL, q, [&] { return launch_vi_split(va, nw, q); })) != hipSuccess)
                 return e;
             if ((e = timed(ctx, LBA_KCLASS_UPDATE, q,
                            [&] {

@@ -297,6 +297,7 @@ struct CholArgs {
     const double *T;
     double *Tn, *dk;
     int stride;                  // unknowns per keyframe in dp: 6, or 15 in an inertial solve
+    double *dpv;                 // inertial solve: the pose part of the joint step, 6 per keyframe
 };
 
 struct UpdArgs {
@@ -431,7 +432,6 @@ struct ViArgs {
     const double *v0, *bg0, *ba0;
     double *v_out, *bg_out, *ba_out;
     const double *dp;            // visual pose step (6 per optimisable keyframe)
-    double *dpv;                 // visual pose step written from the joint one
     const double *vdp;           // joint step (15 per optimisable keyframe)
     const double *red;           // visual reduced system (packed lower S, then r)
     double *vred;                // joint reduced system
@@ -446,8 +446,7 @@ struct ViArgs {
 hipError_t launch_vi_setup(const ViArgs &a, hipStream_t s);
 hipError_t launch_vi_check(const ViArgs &a, hipStream_t s);
 hipError_t launch_vi_eval(const ViArgs &a, hipStream_t s);
-hipError_t launch_vi_system(const ViArgs &a, int n_windows, hipStream_t s);
-hipError_t launch_vi_split(const ViArgs &a, int n_windows, hipStream_t s);
+hipError_t launch_vi_system(const ViArgs &a, int n_windows, int max_n, hipStream_t s);
 hipError_t launch_vi_finish(const ViArgs &a, hipStream_t s);
 
 hipError_t launch_linearize(const LinArgs &a, int ntiles, int passes, size_t lds, bool mixed, hipStream_t s);
