@@ -113,236 +113,239 @@ __device__ void rot_jr(const double *w, double *J, bool inverse) {
     for (int i = 0; i < 9; ++i) J[i] = (i % 4 == 0 ? 1.0 : 0.0) + a * W[i] + b * W2[i];
 }
 
-// body rotation R_cw^T R_cb and position R_cw^T (t_cb - t_cw) of a camera pose
-__device__ __forceinline__ void body_of(const double *T, const double *Tcb, double *Rb, double *pb) {
-    double Rc[9], Rcb[9];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            Rc[i * 3 + j] = T[i * 4 + j];
-            Rcb[i * 3 + j] = Tcb[i * 4 + j];
-        }
-    mtm3(Rc, Rcb, Rb);
-    const double d[3] = {Tcb[3] - T[3], Tcb[7] - T[7], Tcb[11] - T[11]};
-    mtv3(Rc, d, pb);
-}
-
-// Residual (and Jacobian when J is not null: 15 x 30, columns (w, u, v, bg, ba) of
-// keyframe i then of keyframe j) of measurement e for poses Ti, Tj and states si, sj
-// (v, bg, ba each).  The left camera twist (w, u) turns the body rotation by -R_cb^T w on
-// the right and moves the body position by R_cw^T ([t_cb]x w - u).
-__device__ void vi_residual_jacobian(const ViArgs &a, int e, const double *Ti, const double *Tj, const double *si,
-                                     const double *sj, double *r, double (*J)[30]) {
-    const ViEdges &E = a.E;
-    const double dt = E.dt[e];
-    double Ri[9], Rj[9], pi[3], pj[3];
-    body_of(Ti, a.Tcb, Ri, pi);
-    body_of(Tj, a.Tcb, Rj, pj);
-    double dbg[3], dba[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        dbg[q] = si[3 + q] - E.bgb[3 * e + q];
-        dba[q] = si[6 + q] - E.bab[3 * e + q];
-    }
-    const double *JRg = E.JRg + 9 * e;
-    double phi[3], Eb[9], dRc[9], RiRj[9], Em[9];
-    mv3(JRg, dbg, phi);
-    rot_exp(phi, Eb);
-    mm3(E.dR + 9 * e, Eb, dRc);
-    mtm3(Ri, Rj, RiRj);
-    mtm3(dRc, RiRj, Em);
-    rot_log(Em, r);
-    double u[3], wv[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        u[q] = sj[q] - si[q] - a.g[q] * dt;
-        wv[q] = pj[q] - pi[q] - si[q] * dt - 0.5 * a.g[q] * dt * dt;
-    }
-    double Ru[3], Rw[3], t1[3], t2[3], t3[3], t4[3];
-    mtv3(Ri, u, Ru);
-    mtv3(Ri, wv, Rw);
-    mv3(E.Jvg + 9 * e, dbg, t1);
-    mv3(E.Jva + 9 * e, dba, t2);
-    mv3(E.Jpg + 9 * e, dbg, t3);
-    mv3(E.Jpa + 9 * e, dba, t4);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        r[3 + q] = Ru[q] - (E.dv[3 * e + q] + t1[q] + t2[q]);
-        r[6 + q] = Rw[q] - (E.dp[3 * e + q] + t3[q] + t4[q]);
-        r[9 + q] = sj[3 + q] - si[3 + q];
-        r[12 + q] = sj[6 + q] - si[6 + q];
-    }
-    if (!J) return;
-    for (int m = 0; m < 15; ++m)
-        for (int c = 0; c < 30; ++c) J[m][c] = 0.0;
-    auto put = [&](int row, int col, const double *M, double scale) {
-        for (int i = 0; i < 3; ++i)
-            for (int j = 0; j < 3; ++j) J[row + i][col + j] = scale * M[i * 3 + j];
-    };
-    // twist maps of both keyframes: rotation -R_cb^T, position R_cw^T [t_cb]x and -R_cw^T
-    double A[9], Pw[2][9], Pu[2][9];
-    {
-        double Rcb[9], tx[9];
-        for (int i = 0; i < 3; ++i)
-            for (int j = 0; j < 3; ++j) {
-                Rcb[i * 3 + j] = a.Tcb[i * 4 + j];
-                A[j * 3 + i] = -a.Tcb[i * 4 + j];
-            }
-        const double tcb[3] = {a.Tcb[3], a.Tcb[7], a.Tcb[11]};
-        skew3(tcb, tx);
-        for (int side = 0; side < 2; ++side) {
-            const double *T = side ? Tj : Ti;
-            double Rc[9];
-            for (int i = 0; i < 3; ++i)
-                for (int j = 0; j < 3; ++j) Rc[i * 3 + j] = T[i * 4 + j];
-            mtm3(Rc, tx, Pw[side]);
-            for (int i = 0; i < 3; ++i)
-                for (int j = 0; j < 3; ++j) Pu[side][i * 3 + j] = -Rc[j * 3 + i];
-        }
-        (void)Rcb;
-    }
-    double RiT[9];
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) RiT[i * 3 + j] = Ri[j * 3 + i];
-    // rotation rows
-    double Jri[9], RjRi[9], M[9], M2[9];
-    rot_jr(r, Jri, true);
-    mtm3(Rj, Ri, RjRi);
-    mm3(Jri, RjRi, M);          // d r_R / d th_i = -M
-    mm3(M, A, M2);
-    put(0, 0, M2, -1.0);
-    mm3(Jri, A, M2);            // d r_R / d th_j = Jri
-    put(0, 15, M2, 1.0);
-    {
-        double Jr[9], EJ[9], T1[9], T2[9];
-        rot_jr(phi, Jr, false);
-        mtm3(Em, Jr, EJ);      // E^T Jr
-        mm3(Jri, EJ, T1);
-        mm3(T1, JRg, T2);
-        put(0, 9, T2, -1.0);
-    }
-    // velocity rows
-    double H[9];
-    skew3(Ru, H);
-    mm3(H, A, M2);
-    put(3, 0, M2, 1.0);
-    put(3, 6, RiT, -1.0);
-    put(3, 21, RiT, 1.0);
-    put(3, 9, E.Jvg + 9 * e, -1.0);
-    put(3, 12, E.Jva + 9 * e, -1.0);
-    // position rows: rotation and position of i, position of j, velocity of i, biases
-    skew3(Rw, H);
-    mm3(H, A, M);
-    mm3(RiT, Pw[0], M2);
-    for (int q = 0; q < 9; ++q) M[q] -= M2[q];
-    put(6, 0, M, 1.0);
-    mm3(RiT, Pu[0], M2);
-    put(6, 3, M2, -1.0);
-    mm3(RiT, Pw[1], M2);
-    put(6, 15, M2, 1.0);
-    mm3(RiT, Pu[1], M2);
-    put(6, 18, M2, 1.0);
-    put(6, 6, RiT, -dt);
-    put(6, 9, E.Jpg + 9 * e, -1.0);
-    put(6, 12, E.Jpa + 9 * e, -1.0);
-    // bias random walks
-    for (int q = 0; q < 3; ++q) {
-        J[9 + q][9 + q] = -1.0;
-        J[9 + q][24 + q] = 1.0;
-        J[12 + q][12 + q] = -1.0;
-        J[12 + q][27 + q] = 1.0;
-    }
-}
-
 // ---- per measurement ---------------------------------------------------------------------
+// One wavefront per measurement.  Its constants, the two keyframes' states and every 3 x 3
+// product are shared out over the lanes (groups of nine per product, one level of products
+// after the other); only the rotation's exponential and logarithm run on one lane, and
+// that chain bounds it.  Everything on one lane, reading its constants as it went, took 11.3
+// us for one window and 17.9 for 64 (mean of linearising and trial cost); 9.6 and 13.9 so.
+struct ViShared {
+    double dR[9], JRg[9], Jvg[9], Jva[9], Jpg[9], Jpa[9];   // the measurement
+    double dv[3], dp[3], bg[3], ba[3], dt;
+    double info[81];
+    double T[2][12], st[2][9];    // keyframes i and j: pose and (v, bg, ba)
+    double Rc[2][9];              // R_cw
+    double Rb[2][9], pb[2][3];    // body rotation R_cw^T R_cb and position R_cw^T (t_cb - t_cw)
+    double A[9], tx[9];           // -R_cb^T, [t_cb]x
+    double Em[9], Hu[9], Hw[9];   // rotation error; [R_i^T u]x, [R_i^T w]x
+    double Jr[9], Jri[9];         // right Jacobian of the bias rotation, inverse one of r_R
+    double P[15][9];              // products
+    double J[15][30], OJ[15][30], r[15], Or[15];
+};
+
+// element q of A B or A^T B (3 x 3, row-major)
+__device__ __forceinline__ double prod3(const double *A, bool trans, const double *B, int q) {
+    const int i = q / 3, j = q - 3 * i, s0 = trans ? 1 : 3, s1 = trans ? 3 : 1;
+    return A[i * s0] * B[j] + A[i * s0 + s1] * B[3 + j] + A[i * s0 + 2 * s1] * B[6 + j];
+}
+
+// The residual of the measurement in sm, and with jac its Jacobian (15 x 30, columns
+// (w, u, v, bg, ba) of keyframe i then of keyframe j).  The left camera twist (w, u) turns
+// the body rotation by -R_cb^T w on the right and moves the body position by
+// R_cw^T ([t_cb]x w - u).
+__device__ __forceinline__ void vi_residual_jacobian(const ViArgs &a, ViShared &sm, int lane, bool jac) {
+    const int grp = lane / 9, q = lane - 9 * grp, qi = q / 3, qj = q - 3 * qi;
+    if (grp < 2) {
+        const double *T = sm.T[grp];
+        sm.Rc[grp][q] = T[4 * qi + qj];
+        sm.Rb[grp][q] = T[qi] * a.Tcb[qj] + T[4 + qi] * a.Tcb[4 + qj] + T[8 + qi] * a.Tcb[8 + qj];
+        if (q < 3) sm.pb[grp][q] = T[q] * (a.Tcb[3] - T[3]) + T[4 + q] * (a.Tcb[7] - T[7]) + T[8 + q] * (a.Tcb[11] - T[11]);
+    } else if (grp == 2) {
+        sm.A[q] = -a.Tcb[4 * qj + qi];
+        const double m = qi == qj ? 0.0 : a.Tcb[4 * (3 - qi - qj) + 3];
+        sm.tx[q] = qj - qi == 1 || qj - qi == -2 ? -m : m;
+    }
+    if (jac)
+        for (int i = lane; i < 450; i += 64) (&sm.J[0][0])[i] = 0.0;
+    wave_sync();
+    const double dt = sm.dt;
+    if (lane == 0) {
+        const double *si = sm.st[0], *sj = sm.st[1];
+        double dbg[3], dba[3], phi[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            dbg[k] = si[3 + k] - sm.bg[k];
+            dba[k] = si[6 + k] - sm.ba[k];
+        }
+        double Eb[9], dRc[9], RiRj[9], Em[9], r[3];
+        mv3(sm.JRg, dbg, phi);
+        rot_exp(phi, Eb);
+        mm3(sm.dR, Eb, dRc);
+        mtm3(sm.Rb[0], sm.Rb[1], RiRj);
+        mtm3(dRc, RiRj, Em);
+        rot_log(Em, r);
+        double u[3], wv[3], Ru[3], Rw[3], t1[3], t2[3], t3[3], t4[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            u[k] = sj[k] - si[k] - a.g[k] * dt;
+            wv[k] = sm.pb[1][k] - sm.pb[0][k] - si[k] * dt - 0.5 * a.g[k] * dt * dt;
+        }
+        mtv3(sm.Rb[0], u, Ru);
+        mtv3(sm.Rb[0], wv, Rw);
+        mv3(sm.Jvg, dbg, t1);
+        mv3(sm.Jva, dba, t2);
+        mv3(sm.Jpg, dbg, t3);
+        mv3(sm.Jpa, dba, t4);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            sm.r[k] = r[k];
+            sm.r[3 + k] = Ru[k] - (sm.dv[k] + t1[k] + t2[k]);
+            sm.r[6 + k] = Rw[k] - (sm.dp[k] + t3[k] + t4[k]);
+            sm.r[9 + k] = sj[3 + k] - si[3 + k];
+            sm.r[12 + k] = sj[6 + k] - si[6 + k];
+        }
+        if (jac) {
+            rot_jr(phi, sm.Jr, false);
+            rot_jr(r, sm.Jri, true);
+            skew3(Ru, sm.Hu);
+            skew3(Rw, sm.Hw);
+#pragma unroll
+            for (int k = 0; k < 9; ++k) sm.Em[k] = Em[k];
+        }
+    }
+    wave_sync();
+    if (!jac) return;
+    const double *const Ri = sm.Rb[0];
+    if (grp < 6) {
+        const double *L = grp == 0 ? sm.Rb[1] : grp == 1 ? sm.Em : grp == 2 ? sm.Hu : grp == 3 ? sm.Hw : sm.Rc[grp - 4];
+        const double *R = grp == 0 ? Ri : grp == 1 ? sm.Jr : grp < 4 ? sm.A : sm.tx;
+        sm.P[grp][q] = prod3(L, grp != 2 && grp != 3, R, q);
+    }
+    wave_sync();
+    if (grp < 7) {   // Jri (Rj^T Ri), Jri (E^T Jr), Jri A, Ri^T (Rc^T [t]x) and Ri^T Rc^T of i and j
+        const double *L = grp < 3 ? sm.Jri : grp < 5 ? Ri : sm.Rc[grp - 5];
+        const double *R = grp < 2 ? sm.P[grp] : grp == 2 ? sm.A : grp < 5 ? sm.P[grp + 1] : Ri;
+        sm.P[6 + grp][grp < 5 ? q : 3 * qj + qi] = prod3(L, grp == 3 || grp == 4, R, q);
+    }
+    wave_sync();
+    if (grp < 2) sm.P[13 + grp][q] = prod3(sm.P[6 + grp], false, grp ? sm.JRg : sm.A, q);
+    wave_sync();
+    const double rt = Ri[3 * qj + qi];   // Ri^T
+#pragma unroll
+    for (int ps = 0; ps < 3; ++ps) {
+        const int blk = grp + 7 * ps;
+        if (grp >= 7 || blk >= 15) continue;
+        int row = 0, col = 0;
+        double v = 0.0;
+        switch (blk) {
+        case 0: row = 0; col = 0; v = -sm.P[13][q]; break;
+        case 1: row = 0; col = 15; v = sm.P[8][q]; break;
+        case 2: row = 0; col = 9; v = -sm.P[14][q]; break;
+        case 3: row = 3; col = 0; v = sm.P[2][q]; break;
+        case 4: row = 3; col = 6; v = -rt; break;
+        case 5: row = 3; col = 21; v = rt; break;
+        case 6: row = 3; col = 9; v = -sm.Jvg[q]; break;
+        case 7: row = 3; col = 12; v = -sm.Jva[q]; break;
+        case 8: row = 6; col = 0; v = sm.P[3][q] - sm.P[9][q]; break;
+        case 9: row = 6; col = 3; v = sm.P[11][q]; break;
+        case 10: row = 6; col = 15; v = sm.P[10][q]; break;
+        case 11: row = 6; col = 18; v = -sm.P[12][q]; break;
+        case 12: row = 6; col = 6; v = -dt * rt; break;
+        case 13: row = 6; col = 9; v = -sm.Jpg[q]; break;
+        case 14: row = 6; col = 12; v = -sm.Jpa[q]; break;
+        }
+        sm.J[row + qi][col + qj] = v;
+    }
+    if (lane < 6) {   // bias random walks
+        sm.J[9 + lane][9 + lane] = -1.0;
+        sm.J[9 + lane][24 + lane] = 1.0;
+    }
+    wave_sync();
+}
+
 __global__ __launch_bounds__(64) void k_vi_eval(ViArgs a) {
-    __shared__ double J[15][30], OJ[15][30], r[15], Or[15];
+    __shared__ ViShared sm;
     const int e = blockIdx.x, lane = threadIdx.x;
     const int w = a.edge_win[e];
     if (a.trial && !a.ctl[w].running) return;
     const WinInfo W = a.win[w];
-    const int ki = W.kf0 + a.E.ei[e], kj = W.kf0 + a.E.ej[e];
-    const int oi = a.opt_map[ki], oj = a.opt_map[kj];
     const ViEdges &E = a.E;
-    if (lane == 0) {
-        double Ti[12], Tj[12], si[9], sj[9];
-        for (int q = 0; q < 9; ++q) {
-            si[q] = a.state[9 * (int64_t)ki + q];
-            sj[q] = a.state[9 * (int64_t)kj + q];
-        }
-        if (a.trial) {
-            const WinInfo V = a.vwin[w];
-            if (oi >= 0) {
-                se3_left_update(a.dp + W.dp_off + 6 * oi, a.T + 12 * (int64_t)ki, Ti);
-                for (int q = 0; q < 9; ++q) si[q] += a.vdp[V.dp_off + 15 * oi + 6 + q];
-            } else {
-                for (int q = 0; q < 12; ++q) Ti[q] = a.T[12 * (int64_t)ki + q];
-            }
-            if (oj >= 0) {
-                se3_left_update(a.dp + W.dp_off + 6 * oj, a.T + 12 * (int64_t)kj, Tj);
-                for (int q = 0; q < 9; ++q) sj[q] += a.vdp[V.dp_off + 15 * oj + 6 + q];
-            } else {
-                for (int q = 0; q < 12; ++q) Tj[q] = a.T[12 * (int64_t)kj + q];
-            }
-            vi_residual_jacobian(a, e, Ti, Tj, si, sj, r, nullptr);
-        } else {
-            for (int q = 0; q < 12; ++q) {
-                Ti[q] = a.T[12 * (int64_t)ki + q];
-                Tj[q] = a.T[12 * (int64_t)kj + q];
-            }
-            vi_residual_jacobian(a, e, Ti, Tj, si, sj, r, J);
-        }
+    const int ki = W.kf0 + E.ei[e], kj = W.kf0 + E.ej[e];
+    const int oi = a.opt_map[ki], oj = a.opt_map[kj];
+    if (lane < 9) {
+        sm.dR[lane] = E.dR[9 * e + lane];
+        sm.JRg[lane] = E.JRg[9 * e + lane];
+        sm.Jvg[lane] = E.Jvg[9 * e + lane];
+        sm.Jva[lane] = E.Jva[9 * e + lane];
+        sm.Jpg[lane] = E.Jpg[9 * e + lane];
+        sm.Jpa[lane] = E.Jpa[9 * e + lane];
     }
-    __syncthreads();
-    // Info r and Info J: the 9 x 9 block, then the two bias blocks (multiples of I)
-    const double *inf = E.info + 81 * (int64_t)e;
+    if (lane < 3) {
+        sm.dv[lane] = E.dv[3 * e + lane];
+        sm.dp[lane] = E.dp[3 * e + lane];
+        sm.bg[lane] = E.bgb[3 * e + lane];
+        sm.ba[lane] = E.bab[3 * e + lane];
+    }
+    if (lane == 0) sm.dt = E.dt[e];
+    for (int i = lane; i < 81; i += 64) sm.info[i] = E.info[81 * (int64_t)e + i];
     const double ibg = E.ibg[e], iba = E.iba[e];
+    {   // half of the lanes per keyframe
+        const int side = lane >> 5, l = lane & 31, k = side ? kj : ki, o = side ? oj : oi;
+        if (l < 12) {
+            sm.T[side][l] = (a.trial && a.Tn ? a.Tn : a.T)[12 * (int64_t)k + l];
+        } else if (l < 21) {
+            double v = a.state[9 * (int64_t)k + l - 12];
+            if (a.trial && o >= 0) v += a.vdp[a.vwin[w].dp_off + 15 * o + 6 + l - 12];
+            sm.st[side][l - 12] = v;
+        }
+        wave_sync();
+        if (a.trial && !a.Tn && l == 0 && o >= 0) {
+            double T[12], Tt[12];
+#pragma unroll
+            for (int q = 0; q < 12; ++q) T[q] = sm.T[side][q];
+            se3_left_update(a.dp + W.dp_off + 6 * o, T, Tt);
+#pragma unroll
+            for (int q = 0; q < 12; ++q) sm.T[side][q] = Tt[q];
+        }
+        wave_sync();
+    }
+    vi_residual_jacobian(a, sm, lane, !a.trial);
+    // Info r and Info J: the 9 x 9 block, then the two bias blocks (multiples of I)
     if (lane < 15) {
         double v;
         if (lane < 9) {
             v = 0.0;
-            for (int k = 0; k < 9; ++k) v += inf[lane * 9 + k] * r[k];
+            for (int k = 0; k < 9; ++k) v += sm.info[lane * 9 + k] * sm.r[k];
         } else {
-            v = (lane < 12 ? ibg : iba) * r[lane];
+            v = (lane < 12 ? ibg : iba) * sm.r[lane];
         }
-        Or[lane] = v;
+        sm.Or[lane] = v;
     }
-    if (!a.trial && lane < 30) {
-        for (int m = 0; m < 15; ++m) {
+    if (!a.trial)
+        for (int i = lane; i < 450; i += 64) {
+            const int m = i / 30, c = i - 30 * m;
             double v;
             if (m < 9) {
                 v = 0.0;
-                for (int k = 0; k < 9; ++k) v += inf[m * 9 + k] * J[k][lane];
+                for (int k = 0; k < 9; ++k) v += sm.info[m * 9 + k] * sm.J[k][c];
             } else {
-                v = (m < 12 ? ibg : iba) * J[m][lane];
+                v = (m < 12 ? ibg : iba) * sm.J[m][c];
             }
-            OJ[m][lane] = v;
+            sm.OJ[m][c] = v;
         }
-    }
-    __syncthreads();
+    wave_sync();
     double *rec = a.ed + (int64_t)e * kViEdgeStride;
     if (lane == 0) {
         double c = 0.0;
-        for (int m = 0; m < 15; ++m) c += r[m] * Or[m];
+        for (int m = 0; m < 15; ++m) c += sm.r[m] * sm.Or[m];
         rec[a.trial ? 1 : 0] = c;
     }
     if (a.trial) return;
     const bool si_opt = oi >= 0, sj_opt = oj >= 0;
     if (lane < 30) {
         double g = 0.0;
-        for (int m = 0; m < 15; ++m) g += J[m][lane] * Or[m];
+        for (int m = 0; m < 15; ++m) g += sm.J[m][lane] * sm.Or[m];
         rec[kViB + lane] = -g;
     }
     for (int idx = lane; idx < 465; idx += 64) {
-        int row = (int)((sqrt(8.0 * idx + 1.0) - 1.0) * 0.5);
+        int row = (int)((sqrtf(8.0f * idx + 1.0f) - 1.0f) * 0.5f);
         while (row * (row + 1) / 2 > idx) --row;
         while ((row + 1) * (row + 2) / 2 <= idx) ++row;
         const int col = idx - row * (row + 1) / 2;
         const bool need = (row < 15 ? si_opt : sj_opt) && (col < 15 ? si_opt : sj_opt);
         double h = 0.0;
         if (need)
-            for (int m = 0; m < 15; ++m) h += J[m][row] * OJ[m][col];
+            for (int m = 0; m < 15; ++m) h += sm.J[m][row] * sm.OJ[m][col];
         rec[kViH + idx] = h;
     }
 }

@@ -975,6 +975,7 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         ca.dk = static_cast<double *>(W_(pl.o_dk));
         ca.stride = pl.vi ? 15 : 6;
     }
+    va_trial.Tn = ca.Tn;
     if (pl.vi) {   // the joint reduced system of 15 Kopt unknowns per window
         ca.win = va.vwin;
         ca.red = va.vred;

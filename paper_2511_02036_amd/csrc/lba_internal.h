@@ -428,6 +428,7 @@ struct ViArgs {
     const int32_t *opt_map;
     Ctl *ctl;
     const double *T;             // current poses
+    const double *Tn;            // trial poses, where the reduced solve forms them (else null)
     double *state;               // per keyframe: v (3), bg (3), ba (3)
     const double *v0, *bg0, *ba0;
     double *v_out, *bg_out, *ba_out;
