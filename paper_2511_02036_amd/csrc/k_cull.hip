@@ -34,7 +34,7 @@ __global__ __launch_bounds__(256) void k_cull_begin(CullArgs a, int general) {
 }
 
 // Bound by the latency of a run's loads, LDS counts and sums, one after the other, with four
-// blocks per compute unit: 28 million observations of 4 million points take 180 us (2.2 TB/s
+// blocks per compute unit: 18 million observations of 2.6 million points take 180 us (1.5 TB/s
 // of its bytes), the zeroing and two passes before it 376.  More LDS for the counts, shorter
 // runs, or registers for six blocks per unit cost 10 to 60% more; four copies of the totals,
 // by lane, are 2% faster than one.
@@ -246,8 +246,8 @@ void launch_cull_check(const CullArgs &a, hipStream_t s) {
 }
 
 void launch_cull(const CullArgs &a, hipStream_t s) {
-    // few observations are bound by the launches, and the single pass is one more (280,000: 23
-    // us in general passes, 26 with it; 5 million: 65 and 49)
+    // few observations are bound by the launches, and the single pass is one more (140,000: 23
+    // us in general passes, 26 with it; 2.6 million: 65 and 49)
     const bool grouped = a.n_obs >= kGrpMinObs;
     hipLaunchKernelGGL(k_cull_begin, dim3((a.n_kf + 255) / 256), dim3(256), 0, s, a, grouped ? 0 : 1);
     if (a.n_obs <= 0) {

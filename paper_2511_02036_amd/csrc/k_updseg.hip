@@ -16,7 +16,7 @@
 //
 // Bound by the latency of a chunk's loads and its LDS round trips (about 1.5 TB/s of its
 // bytes on batches).  Per step against k_update: one window of 64,000
-// observations 7 us (10), 48 windows of 56,000 44 us (33; the positions that it reads and
+// observations 7 us (10), 48 windows of 1.4 million 44 us (33; the positions that it reads and
 // writes in order save that back in k_linseg, whose point loads would be gathers).
 #include "lba_internal.h"
 

@@ -304,9 +304,9 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
     // A chunk holds at most 64 observations (about 52 in the mean).  A segment's record is 16
     // KB, written once and read once, so fewer and longer segments save traffic; but about
     // 2048 wavefronts are resident, and segments of uneven length leave the last of them
-    // alone.  Measured, linearisation + reduction + update per step: 48 windows of 8000
-    // points 391 us in 1,600 segments, 245 in 2,000, 223 in 4,100, 230 in 5,700; one window
-    // of 8000 points 48 us in 1,200 segments, 37 in 600.  A range of positions holds about
+    // alone.  Measured, linearisation + reduction + update per step: 48 windows of 1.4
+    // million observations 380 us with at most 32 chunks per segment, 245 with 13, 223 with
+    // 7, 230 with 5; one window of 64,000 observations 48 us with one, 37 with two.  A range of positions holds about
     // four segments (the last one of a range is cut short).
     if (!pl.mixed && P->n_obs > 0 && P->n_pt <= kSegMaxPoints) {
         const int64_t chunks = P->n_obs / 52 + 1;
