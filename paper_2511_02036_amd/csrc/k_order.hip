@@ -6,10 +6,14 @@
 // blocks of the reduced system and each touched block gathers many pairs.  The sums it
 // forms are the same (the Schur complement does not depend on the order of the points).
 //
-// Windows with few optimisable keyframes (min_kopt or fewer), whose chunks touch few
-// camera blocks in any order, keep the index order (k_order_identity writes it): the sort
-// does not pay below 20 in the general form, and below 11 any point suits a segment.  The others use two kernels, run once per
-// solve after the input checks:
+// Windows with few optimisable keyframes, whose chunks touch few camera blocks in any order,
+// keep the index order (k_order_identity writes it): up to ten where segments follow, since
+// any point suits a segment there, up to 20 (kSortMinKopt) in the general form, where the sort
+// does not pay below (18 keyframes, 80,000 observations: a solve in index order 1,980 us, sorted
+// 2,820).  A problem that turns out not to suit the segments takes the general form's order:
+// k_order_keys finds the unsuitable points before anything is sorted, and where the plan finds
+// itself over its capacities the index order is written again.  The others use two kernels, run
+// once per solve after the input checks:
 //   k_order_keys  grid (x, window), one thread per point: key = lowest | highest << 6 (Kopt
 //                 for both when no optimisable keyframe observes the point) | observations
 //                 << 12, and the set of its optimisable keyframes;
@@ -35,8 +39,11 @@ constexpr int kOrdThreads = 1024;
 constexpr int kOrdWaves = kOrdThreads / kWave;
 constexpr int kBuckets = 64;             // digit range: optimisable keyframe index, Kopt = none
 
+constexpr int kSortMinKopt = 20;         // the general form sorts windows with more optimisable keyframes
+
 __device__ __forceinline__ bool sorted_window(const OrderArgs &a, const WinInfo &W) {
-    return a.by_keyframes && W.Kopt > a.min_kopt;
+    const bool segments = a.max_cams > 0 && !a.err[kSegInfoGeneral];
+    return a.by_keyframes && W.Kopt > (segments ? a.max_cams : kSortMinKopt);
 }
 static_assert(kMaxKoptFP64 < kBuckets && kMaxKoptMixed < kBuckets, "keyframe digit range");
 
@@ -75,7 +82,7 @@ __global__ __launch_bounds__(256) void k_order_keys(OrderArgs a) {
         a.keys[P] = lo | (hi << 6) | ((unsigned)(o1 - o0) << 12);
         if (a.max_cams == 0) continue;
         a.kfmask[P] = set;
-        if (dup || __popcll(set) > a.max_cams) a.err[kSegInfoGeneral] = 1;
+        if (dup || __popcll(set) > a.max_cams) a.err[kSegInfoGeneral] = kSegUnsuited;
     }
 }
 
@@ -228,11 +235,21 @@ hipError_t launch_order_gather(const OrderArgs &a, bool mask, hipStream_t s) {
 hipError_t launch_order(const OrderArgs &a, int n_windows, int max_points, int max_kopt, hipStream_t s) {
     if (n_windows <= 0) return hipSuccess;
     const int bx = std::max(1, std::min(64, (max_points + 255) / 256));
-    hipLaunchKernelGGL(k_order_identity, dim3(bx, n_windows), dim3(256), 0, s, a);
-    const bool sort = a.by_keyframes && max_kopt > a.min_kopt;
+    const bool sort = a.by_keyframes && max_kopt > (a.max_cams > 0 ? a.max_cams : kSortMinKopt);
     if (sort || a.max_cams > 0) hipLaunchKernelGGL(k_order_keys, dim3(bx, n_windows), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_order_identity, dim3(bx, n_windows), dim3(256), 0, s, a);
     if (sort)
         hipLaunchKernelGGL(k_order, dim3(max_kopt + 1, n_windows), dim3(kOrdThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+// the general form's order after segments were planned in vain: index order again in the windows
+// that only the segments have sorted
+hipError_t launch_order_general(OrderArgs a, int n_windows, int max_points, hipStream_t s) {
+    if (n_windows <= 0) return hipSuccess;
+    a.max_cams = 0;
+    const int bx = std::max(1, std::min(64, (max_points + 255) / 256));
+    hipLaunchKernelGGL(k_order_identity, dim3(bx, n_windows), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -134,7 +134,7 @@ __device__ void seg_range(const SegPlanArgs &a, int r, int lane, SegStage &st) {
         a.base[3 * (int64_t)r] = nseg;
         a.base[3 * (int64_t)r + 1] = nchunk;
         a.base[3 * (int64_t)r + 2] = rec;
-        if (flag) a.info[kSegInfoGeneral] = 1;
+        if (flag) a.info[kSegInfoGeneral] = kSegOver;
     }
 }
 
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kScanThreads) void k_seg_scan(SegPlanArgs a) {
         a.base[3 * (int64_t)a.n_ranges] = tot[0];   // end of the last range's segments
         a.info[kSegInfoCount] = (int32_t)min(tot[0], (long long)INT32_MAX);
         a.info[kSegInfoChunks] = (int32_t)min(tot[1], (long long)INT32_MAX);
-        if (tot[0] > a.seg_cap || tot[1] > a.chunk_cap || tot[2] > a.rec_cap) a.info[kSegInfoGeneral] = 1;
+        if (tot[0] > a.seg_cap || tot[1] > a.chunk_cap || tot[2] > a.rec_cap) a.info[kSegInfoGeneral] = kSegOver;
     }
 }
 

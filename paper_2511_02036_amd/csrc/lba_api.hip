@@ -809,7 +809,6 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         oa.tmp = static_cast<int32_t *>(W_(pl.o_ptmp));
         oa.pinfo = d_pinfo;
         oa.max_cams = pl.ranges.empty() ? 0 : kSegCams;
-        oa.min_kopt = pl.mixed ? 20 : 10;
         oa.by_keyframes = 1;
         oa.n_pt = P->n_pt;
         oa.obs = ob;
@@ -854,7 +853,11 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     HIPCHK(collect_timing(ctx));
     if (info[0]) return set_error(ctx, LBA_ERR_INVALID_ARGUMENT, "invalid input: %s", describe_input_error(info[0]).c_str());
     if (info[kSegInfoGeneral]) use_seg = false;
-    if (!use_seg) HIPCHK(timed(ctx, LBA_KCLASS_ORDER, s, [&] { return launch_order_gather(oa, false, s); }));
+    if (!use_seg)
+        HIPCHK(timed(ctx, LBA_KCLASS_ORDER, s, [&] {
+            hipError_t e = info[kSegInfoGeneral] == kSegOver ? launch_order_general(oa, nw, pl.max_pts, s) : hipSuccess;
+            return e != hipSuccess ? e : launch_order_gather(oa, false, s);
+        }));
 
     const int ntiles = (int)pl.tiles.size();
     LinArgs la;

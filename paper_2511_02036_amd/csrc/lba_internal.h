@@ -141,7 +141,9 @@ static_assert(kMaxKf <= 128, "a word holds 7 bits of keyframe");
 constexpr int kSegNoCam = 15;      // camera place of an observation on a fixed keyframe
 constexpr uint32_t kSegInactive = 1u << 23;   // word of an observation left out in round 2
 // a.info: 0 input checks, then
-constexpr int kSegInfoGeneral = 2;   // the general linearisation is needed
+constexpr int kSegInfoGeneral = 2;   // the general linearisation is needed:
+constexpr int kSegUnsuited = 1;      // ... an unsuitable point or observation, found before the sort
+constexpr int kSegOver = 2;          // ... a plan over its capacities, found after it
 constexpr int kSegInfoCount = 3;     // segments
 constexpr int kSegInfoChunks = 4;    // chunks
 
@@ -158,7 +160,6 @@ struct OrderArgs {
     int4 *pinfo;                 // result, per position of the order: point, first observation,
                                  // observation count, place of the first observation (n_pt)
     int max_cams;                // optimisable keyframes of a segment (0: no segment plan follows)
-    int min_kopt;                // windows with more optimisable keyframes are sorted
     int by_keyframes;            // 1: sort the windows with many optimisable keyframes by
                                  // keyframes; 0: index order everywhere
     int32_t n_pt;
@@ -469,6 +470,7 @@ hipError_t launch_decide(const DecideArgs &a, int n_windows, hipStream_t s);
 hipError_t launch_init_reduce(const InitReduceArgs &a, int n_windows, hipStream_t s);
 hipError_t launch_setup(const MiscArgs &a, int n_windows, hipStream_t s);
 hipError_t launch_order(const OrderArgs &a, int n_windows, int max_points, int max_kopt, hipStream_t s);
+hipError_t launch_order_general(OrderArgs a, int n_windows, int max_points, hipStream_t s);
 hipError_t launch_order_gather(const OrderArgs &a, bool mask, hipStream_t s);
 hipError_t launch_validate(const MiscArgs &a, int n_windows, int64_t max_obs, hipStream_t s);
 hipError_t launch_flags(const MiscArgs &a, int n_windows, int64_t max_obs, hipStream_t s);

@@ -1,0 +1,132 @@
+"""The general form of the FP64 step (tiles of points, pairs of observations listed), which a
+problem takes where the segment form does not suit it: a point seen by more than ten optimisable
+keyframes, a repeated observation, or a segment plan over its capacities.  Against the FP64 CPU
+oracle, with the form that ran asserted: a solve's `order` class is launched twice in the segment
+form (order, plan) and three times in the general one (and the observations copied in order).
+
+The bar is the suite's FP64 bar (1e-9 in the cost, 1e-8 in the states)."""
+import numpy as np
+import pytest
+
+from oracle import lbaref
+from paper_2511_02036_amd import synth
+from tests.parity import assert_fp64_parity, window_slice
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2511_02036_amd import lba  # noqa: E402
+
+DEV = torch.device("cuda:0")
+
+
+def _window(seed, kopt, M, nobs, fixed=4):
+    return synth.make_window(np.random.default_rng(seed), trajectory="arc", K=kopt + fixed, n_fixed=fixed, M=M, nobs=nobs,
+                             stereo_p=0.6)
+
+
+def _pick(w, keep):
+    out = dict(w)
+    for k in ("obs_kf", "obs_pt", "obs_type", "obs_oct", "is_outlier_true"):
+        out[k] = np.ascontiguousarray(w[k][keep])
+    out["obs_z"] = np.ascontiguousarray(w["obs_z"][:, keep])
+    return out
+
+
+def _repeat_one(w):
+    """One observation of an optimisable keyframe twice."""
+    i = int(np.flatnonzero(np.asarray(w["fixed"])[w["obs_kf"]] == 0)[len(w["obs_kf"]) // 3])
+    return _pick(w, np.insert(np.arange(len(w["obs_kf"])), i, i))
+
+
+def _scattered(seed, kopt, M, per=5):
+    """Points seen by any `per` keyframes: few points share ten, so that the plan needs far more
+    segments than observations of neighbouring keyframes do."""
+    w = _window(seed, kopt, M, (kopt + 4, kopt + 4))
+    r = np.random.default_rng(seed).random(len(w["obs_kf"]))
+    o = np.lexsort((r, w["obs_pt"]))
+    pt = w["obs_pt"][o]
+    first = np.concatenate([[0], np.flatnonzero(np.diff(pt)) + 1])
+    rank = np.arange(len(pt)) - np.repeat(first, np.diff(np.append(first, len(pt))))
+    return _pick(w, np.sort(o[rank < per]))
+
+
+def _most_seen(w):
+    on = np.asarray(w["fixed"])[w["obs_kf"]] == 0
+    return int(np.bincount(w["obs_pt"][on], minlength=1).max())
+
+
+def _run(data, vi=None, **options):
+    """A solve with kernels launched one by one, and the form it took."""
+    ctx = lba.Context(0, **options)
+    prob = lba.DeviceProblem(data, device=DEV)
+    s = lba.Solver(ctx, prob) if vi is None else lba.InertialSolver(ctx, prob, lba.DeviceInertial(vi, device=DEV))
+    ctx.profile(True)
+    s.run()
+    return s, {2: "segments", 3: "general"}[ctx.profile_read()["order"][0]]
+
+
+def _out(s):
+    return dict(T=s.T_out.cpu().numpy(), X=s.X_out.cpu().numpy(), outlier=s.outlier.cpu().numpy().astype(bool),
+                stats=s.stats_dicts())
+
+
+def _parity(data, g, windows):
+    if len(windows) == 1:
+        assert_fp64_parity(windows[0], g["T"], g["X"], g["outlier"], g["stats"][0], lbaref.solve(windows[0]))
+        return
+    for i, w in enumerate(windows):
+        ks, ps, os_ = window_slice(data, i)
+        assert_fp64_parity(w, g["T"][ks], g["X"][ps], g["outlier"][os_], g["stats"][i], lbaref.solve(w))
+
+
+def _same(a, b):
+    for k in ("T", "X", "outlier"):
+        np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+    for sa, sb in zip(a["stats"], b["stats"]):
+        np.testing.assert_equal(sa, sb)
+
+
+def _in_index_order(s):
+    """Whether the workspace holds the linearisation order (point, first observation,
+    observations, place) with the points in index order."""
+    pt = s.prob.obs_pt.cpu().numpy()
+    n = s.prob.X.shape[0]
+    first = np.searchsorted(pt, np.arange(n + 1)).astype(np.int32)
+    rec = np.stack([np.arange(n), first[:-1], np.diff(first), first[:-1]], axis=1).astype(np.int32)
+    return rec.tobytes() in s.ws.cpu().numpy().tobytes()
+
+
+@pytest.mark.parametrize("kopt, index_order", [(10, True), (11, True), (15, True), (20, True), (21, False)])
+@pytest.mark.parametrize("why", ["repeat", "long", "plan"])
+def test_order_of_the_general_form(why, kopt, index_order):
+    """The general form sorts windows of more than 20 optimisable keyframes, whatever turned the
+    segments down; the segments sort from 11."""
+    if why == "repeat":
+        w = _repeat_one(_window(600 + kopt, kopt, 400, (3, 8)))
+    elif why == "long":
+        if kopt < 11:
+            pytest.skip("no point has more than ten")
+        w = _window(600 + kopt, kopt, 400, (kopt + 4, kopt + 4))
+        assert _most_seen(w) > 10
+    else:
+        if kopt < 20:   # (at 15 the plan of these points fits)
+            pytest.skip("such a plan fits")
+        w = _scattered(600 + kopt, kopt, 6000)
+        assert _most_seen(w) <= 10
+    print(f"case general order {why} kopt={kopt} N={len(w['obs_kf'])}", flush=True)
+    s, form = _run(w)
+    assert form == "general"
+    assert _in_index_order(s) == index_order
+
+
+def test_order_of_the_segments():
+    for kopt, index_order in ((10, True), (11, False)):
+        w = _window(640, kopt, 400, (3, 8))
+        print(f"case segment order kopt={kopt} N={len(w['obs_kf'])}", flush=True)
+        s, form = _run(w)
+        assert form == "segments"
+        assert _in_index_order(s) == index_order
