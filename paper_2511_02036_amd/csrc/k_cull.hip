@@ -9,10 +9,11 @@
 // Observations grouped by ascending point, as the bundle adjustment holds them, take one
 // pass (k_cull_grouped): a block owns the points whose first observation lies in its run
 // of observations, counts them in LDS, writes their counters once (zeros included) and
-// tests its observations against the counts in LDS.  The pass finds out by itself: any
-// descent, index out of range, point with more than kGrpTail observations past a run's end
-// or run over too many points raises the flag, and then three general passes run over
-// zeroed counters (without the flag they return at once):
+// tests its observations against the counts in LDS.  k_cull_order decides that first, from the
+// point indices alone: any descent, index out of range, point with kGrpTail or more
+// observations past a run's end (and more after it) or run over too many points raises the
+// flag, and then three general passes run over zeroed counters (without the flag they return
+// at once):
 //   1. counters[j][o] += 1 for every active observation (integer atomics: exact, and
 //      independent of the order);
 //   2. per active observation (k, j, o): others = counters[j][0 .. o + slack] summed,
@@ -33,36 +34,69 @@ __global__ __launch_bounds__(256) void k_cull_begin(CullArgs a, int general) {
     if (k == 0) a.cull[0] = general;
 }
 
+constexpr int kGrpThreads = 256, kGrpRun = 2048, kGrpTail = 256, kGrpCounts = 4096, kGrpTiles = 16, kGrpSpan = 512,
+              kGrpCopies = 4, kGrpMinObs = 1 << 20;
+constexpr int kGrpOrderBlocks = 4096;
+
+// Whether the single pass can take the observations.  Reads the point indices only, run by
+// run, and stops once any block has raised the flag.  Deciding this within the single pass wasted
+// the pass where a descent came late: 5 million observations of 2,000 random keyframes 1,219 us
+// so, 743 now, 738 in general passes alone; bound by reading the indices (18 us of 310 at 28
+// million in order).
+__global__ __launch_bounds__(kGrpThreads) void k_cull_order(CullArgs a) {
+    const int tid = threadIdx.x, n = a.n_obs;
+    const int64_t most = (int64_t)kGrpTiles * (kGrpCounts / a.n_levels);   // points of a run
+    for (int64_t r0 = (int64_t)blockIdx.x * kGrpRun; r0 < n; r0 += (int64_t)gridDim.x * kGrpRun) {
+        const uint8_t raised = *(volatile uint8_t *)a.cull;
+        const int last = n - 1;
+        const int first = a.pt[max((int)r0 - 1, 0)], final = a.pt[min((int64_t)last, r0 + kGrpRun - 1)],
+                  tail = a.pt[min((int64_t)last, r0 + kGrpRun + kGrpTail - 1)];
+        int pt[kGrpRun / kGrpThreads], before[kGrpRun / kGrpThreads];
+#pragma unroll
+        for (int u = 0; u < kGrpRun / kGrpThreads; ++u) {   // (past the end: the last one again)
+            const int i = (int)min((int64_t)last, r0 + tid + u * kGrpThreads);
+            pt[u] = a.pt[i];
+            before[u] = a.pt[max(i - 1, 0)];
+        }
+        if (raised) return;
+        bool bad = false;
+#pragma unroll
+        for (int u = 0; u < kGrpRun / kGrpThreads; ++u) bad = bad || pt[u] < 0 || pt[u] >= a.n_pt || before[u] > pt[u];
+        // the run's points, and its last point's tail
+        const bool end = r0 + kGrpRun >= n;
+        const int64_t p0 = r0 == 0 ? 0 : (int64_t)first + 1, p1 = end ? a.n_pt : (int64_t)final + 1;
+        bad = bad || p1 - p0 > most || (r0 + kGrpRun + kGrpTail < n && tail == final);
+        if (__any(bad) && (tid & 63) == 0) a.cull[0] = 1;
+    }
+}
+
 // Bound by the latency of a run's loads, LDS counts and sums, one after the other, with four
 // blocks per compute unit: 18 million observations of 2.6 million points take 180 us (1.5 TB/s
 // of its bytes), the zeroing and two passes before it 376.  More LDS for the counts, shorter
 // runs, or registers for six blocks per unit cost 10 to 60% more; four copies of the totals,
-// by lane, are 2% faster than one.
-constexpr int kGrpThreads = 256, kGrpRun = 2048, kGrpTail = 256, kGrpCounts = 4096, kGrpTiles = 16, kGrpSpan = 512,
-              kGrpCopies = 4, kGrpMinObs = 1 << 20;
-
+// by lane, are 2% faster than one.  With the flag raised the launch zeroes the counters instead.
 __global__ __launch_bounds__(kGrpThreads) void k_cull_grouped(CullArgs a) {
     __shared__ __align__(16) int cnt[kGrpCounts];
     __shared__ int h[kGrpCopies][kGrpSpan];   // observations | redundant << 16, by lane
-    __shared__ int s_at[2], s_k[2], s_raised, s_bad;
+    __shared__ int s_at[2], s_k[2];
     constexpr int kPer = (kGrpRun + kGrpTail) / kGrpThreads;
     const int tid = threadIdx.x, L = a.n_levels, n = a.n_obs;
+    if (a.cull[0]) {   // (uniform) the general passes start from zeros
+        const int64_t nc = (int64_t)a.n_pt * L;
+        for (int64_t i = blockIdx.x * (int64_t)kGrpThreads + tid; i < nc; i += (int64_t)gridDim.x * kGrpThreads) a.counters[i] = 0;
+        return;
+    }
+    if (blockIdx.x * (int64_t)kGrpRun >= n) return;
     const int i0 = blockIdx.x * kGrpRun, i1 = min(n, i0 + kGrpRun);
     if (tid < 2) {
         s_at[tid] = tid == 0 ? (i0 == 0 ? 0 : n) : n;
         s_k[tid] = tid == 0 ? 0x7fffffff : -1;
     }
-    if (tid == 2) {
-        s_raised = a.cull[0];   // (by another block already)
-        s_bad = 0;
-    }
     for (int k = tid; k < kGrpCopies * kGrpSpan; k += kGrpThreads) (&h[0][0])[k] = 0;
     __syncthreads();
-    if (s_raised) return;
     // the run and what follows it; the first observations of a point at or after i0 and i1
-    // (the run of a point that starts there), and everything in order
+    // (the run of a point that starts there)
     int pt[kPer], kf[kPer], oc[kPer];
-    bool bad = false;
     int lo = n, hi = n;
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
@@ -72,31 +106,17 @@ __global__ __launch_bounds__(kGrpThreads) void k_cull_grouped(CullArgs a) {
         oc[u] = a.oct[ic];
         if (a.active && !a.active[ic]) oc[u] = -1;
         const int before = a.pt[max(ic - 1, 0)];
-        if (i < n) {
-            bad = bad || pt[u] < 0 || pt[u] >= a.n_pt || before > pt[u];
-            if (i > 0 && before != pt[u]) {
-                if (i >= i1) hi = min(hi, i);
-                lo = min(lo, i);
-            }
+        if (i > 0 && i < n && before != pt[u]) {
+            if (i >= i1) hi = min(hi, i);
+            lo = min(lo, i);
         }
     }
     if (lo < n) atomicMin(&s_at[0], lo);
     if (hi < n) atomicMin(&s_at[1], hi);
-    if (bad) s_bad = 1;
     __syncthreads();
-    const int b0 = s_at[0], b1 = s_at[1];
-    // (no start within the tail: fine only where the observations end there)
-    const bool far = (b0 > i0 + kGrpRun + kGrpTail || b1 > i1 + kGrpTail) && i0 + kGrpRun + kGrpTail < n;
-    int p0 = 0, p1 = 0;
-    if (!s_bad && !far) {
-        p0 = b0 == 0 ? 0 : max(a.pt[b0 - 1], -1) + 1;   // (another block's, not yet checked)
-        p1 = b1 == n ? a.n_pt : a.pt[b1 - 1] + 1;
-    }
+    const int b0 = s_at[0], b1 = s_at[1];   // (none up to the end of the observations: n)
+    const int p0 = b0 == 0 ? 0 : a.pt[b0 - 1] + 1, p1 = b1 == n ? a.n_pt : a.pt[b1 - 1] + 1;
     const int tile = kGrpCounts / L;
-    if (s_bad || far || p1 - p0 > kGrpTiles * tile) {   // (uniform)
-        if (tid == 0) a.cull[0] = 1;
-        return;
-    }
     int kmin = 0x7fffffff, kmax = -1;
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
@@ -151,14 +171,6 @@ __global__ __launch_bounds__(kGrpThreads) void k_cull_grouped(CullArgs a) {
     }
 }
 
-// the general passes start from zeros
-__global__ __launch_bounds__(256) void k_cull_zero(CullArgs a) {
-    if (!a.cull[0]) return;
-    const int64_t n = (int64_t)a.n_pt * a.n_levels;
-    for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) a.counters[i] = 0;
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < a.n_kf; k += gridDim.x * 256) a.kf_obs[k] = a.kf_red[k] = 0;
-}
-
 __global__ __launch_bounds__(256) void k_cull_count(CullArgs a) {
     if (!a.cull[0]) return;
     for (int i = blockIdx.x * 256 + threadIdx.x; i < a.n_obs; i += gridDim.x * 256) {
@@ -170,19 +182,30 @@ __global__ __launch_bounds__(256) void k_cull_count(CullArgs a) {
 }
 
 constexpr int kCullSpan = 1024;   // keyframes per block summed in LDS
+constexpr int kRedRun = 512;      // observations of a block (2048: observations by keyframe 6% slower)
 
-__global__ __launch_bounds__(256) void k_cull_redundant(CullArgs a, int per_block) {
+__global__ __launch_bounds__(256) void k_cull_redundant(CullArgs a) {
     __shared__ int h_obs[kCullSpan], h_red[kCullSpan];
     __shared__ int wmin[4], wmax[4];
     if (!a.cull[0]) return;
-    const int i0 = blockIdx.x * per_block, i1 = min(a.n_obs, i0 + per_block);
+    const int64_t i0 = (int64_t)blockIdx.x * kRedRun;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    // keyframe span of the block
+    // the block's observations, every load issued before any is used, and their keyframe span
+    constexpr int kPer = kRedRun / 256;
+    int kf[kPer], pt[kPer], oc[kPer], on[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int64_t i = min(i0 + threadIdx.x + 256 * u, (int64_t)a.n_obs - 1);   // (past the end: the last one again)
+        kf[u] = a.kf[i];
+        pt[u] = a.pt[i];
+        oc[u] = a.oct[i];
+        on[u] = a.active ? a.active[i] : 1;
+    }
     int kmin = 0x7fffffff, kmax = -1;
-    for (int i = i0 + threadIdx.x; i < i1; i += 256) {
-        const int k = a.kf[i];
-        kmin = min(kmin, k);
-        kmax = max(kmax, k);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        kmin = min(kmin, kf[u]);
+        kmax = max(kmax, kf[u]);
     }
     for (int o = 32; o > 0; o >>= 1) {
         kmin = min(kmin, __shfl_xor(kmin, o, 64));
@@ -198,10 +221,10 @@ __global__ __launch_bounds__(256) void k_cull_redundant(CullArgs a, int per_bloc
     kmax = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
     const bool local = kmax >= kmin && kmax - kmin < kCullSpan;
     const int L = a.n_levels;
-    for (int i = i0 + threadIdx.x; i < i1; i += 256) {
-        if (a.active && !a.active[i]) continue;
-        const int k = a.kf[i], j = a.pt[i], o = a.oct[i];
-        if (k < 0 || k >= a.n_kf || j < 0 || j >= a.n_pt || o >= L) continue;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int k = kf[u], j = pt[u], o = oc[u];
+        if (i0 + threadIdx.x + 256 * u >= a.n_obs || !on[u] || k < 0 || k >= a.n_kf || j < 0 || j >= a.n_pt || o >= L) continue;
         const int top = min(L - 1, o + a.slack);
         const int32_t *c = a.counters + (size_t)j * L;
         int others = -1;   // the observation itself is one of the counted
@@ -246,27 +269,28 @@ void launch_cull_check(const CullArgs &a, hipStream_t s) {
 }
 
 void launch_cull(const CullArgs &a, hipStream_t s) {
-    // few observations are bound by the launches, and the single pass is one more (140,000: 23
-    // us in general passes, 26 with it; 2.6 million: 65 and 49)
-    const bool grouped = a.n_obs >= kGrpMinObs;
+    // few observations are bound by the launches, and the single pass takes one more (140,000: 23
+    // us in general passes, 26 with it; 2.6 million: 65 and 49); its indices are 32-bit, up to the
+    // end of the last run's tail
+    const int64_t nc = (int64_t)a.n_pt * a.n_levels;
+    const bool grouped = a.n_obs >= kGrpMinObs && a.n_obs <= INT32_MAX - kGrpRun - kGrpTail;
     hipLaunchKernelGGL(k_cull_begin, dim3((a.n_kf + 255) / 256), dim3(256), 0, s, a, grouped ? 0 : 1);
-    if (a.n_obs <= 0) {
-        launch_fill_i32(a.counters, (int64_t)a.n_pt * a.n_levels, 0, s);
-    } else {
-        prof_begin(LMAP_KCLASS_CULL_COUNT, s);
-        if (grouped)
-            hipLaunchKernelGGL(k_cull_grouped, dim3((a.n_obs + kGrpRun - 1) / kGrpRun), dim3(kGrpThreads), 0, s, a);
-        const int64_t nc = std::max<int64_t>((int64_t)a.n_pt * a.n_levels, a.n_kf);
-        hipLaunchKernelGGL(k_cull_zero, dim3((unsigned)std::min<int64_t>(4096, (nc + 255) / 256)), dim3(256), 0, s, a);
-        prof_end(s);
+    if (!grouped) launch_fill_i32(a.counters, nc, 0, s);
+    if (a.n_obs > 0) {
+        if (grouped) {
+            const int runs = (a.n_obs + kGrpRun - 1) / kGrpRun;
+            prof_begin(LMAP_KCLASS_CULL_COUNT, s);
+            hipLaunchKernelGGL(k_cull_order, dim3(std::min(runs, kGrpOrderBlocks)), dim3(kGrpThreads), 0, s, a);
+            const int zero = (int)std::min<int64_t>(4096, (nc + 1023) / 1024);
+            hipLaunchKernelGGL(k_cull_grouped, dim3(std::max(runs, zero)), dim3(kGrpThreads), 0, s, a);
+            prof_end(s);
+        }
         const unsigned blocks = (unsigned)std::min(8192, (a.n_obs + 255) / 256);
         prof_begin(LMAP_KCLASS_CULL_COUNT, s);
         hipLaunchKernelGGL(k_cull_count, dim3(blocks), dim3(256), 0, s, a);
         prof_end(s);
-        const int per_block = 2048;
         prof_begin(LMAP_KCLASS_CULL_REDUNDANT, s);
-        hipLaunchKernelGGL(k_cull_redundant, dim3((a.n_obs + per_block - 1) / per_block), dim3(256), 0, s, a,
-                           per_block);
+        hipLaunchKernelGGL(k_cull_redundant, dim3((unsigned)(((int64_t)a.n_obs + kRedRun - 1) / kRedRun)), dim3(256), 0, s, a);
         prof_end(s);
     }
     prof_begin(LMAP_KCLASS_CULL_DECIDE, s);
