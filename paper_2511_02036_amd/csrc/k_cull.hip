@@ -22,7 +22,8 @@
 //      a short range, else with global atomics;
 //   3. per keyframe: culled if not protected, it has observations and
 //      den * redundant >= num * observations.
-// The flag is the first byte of cull, which pass 3 writes afterwards: it belongs to the call.
+// The flag is bit 0 of cull's first byte, which pass 3 writes afterwards: it belongs to the call.
+// (Bit 1 keeps protect's first byte, so that protect and cull may be one array.)
 #include "lmap_internal.h"
 
 namespace lmap {
@@ -31,7 +32,7 @@ namespace lmap {
 __global__ __launch_bounds__(256) void k_cull_begin(CullArgs a, int general) {
     const int k = blockIdx.x * 256 + threadIdx.x;
     if (k < a.n_kf) a.kf_obs[k] = a.kf_red[k] = 0;
-    if (k == 0) a.cull[0] = general;
+    if (k == 0) a.cull[0] = general | (a.protect && a.protect[0] ? 2 : 0);
 }
 
 constexpr int kGrpThreads = 256, kGrpRun = 2048, kGrpTail = 256, kGrpCounts = 4096, kGrpTiles = 16, kGrpSpan = 512,
@@ -58,7 +59,7 @@ __global__ __launch_bounds__(kGrpThreads) void k_cull_order(CullArgs a) {
             pt[u] = a.pt[i];
             before[u] = a.pt[max(i - 1, 0)];
         }
-        if (raised) return;
+        if (raised & 1) return;
         bool bad = false;
 #pragma unroll
         for (int u = 0; u < kGrpRun / kGrpThreads; ++u) bad = bad || pt[u] < 0 || pt[u] >= a.n_pt || before[u] > pt[u];
@@ -66,7 +67,7 @@ __global__ __launch_bounds__(kGrpThreads) void k_cull_order(CullArgs a) {
         const bool end = r0 + kGrpRun >= n;
         const int64_t p0 = r0 == 0 ? 0 : (int64_t)first + 1, p1 = end ? a.n_pt : (int64_t)final + 1;
         bad = bad || p1 - p0 > most || (r0 + kGrpRun + kGrpTail < n && tail == final);
-        if (__any(bad) && (tid & 63) == 0) a.cull[0] = 1;
+        if (__any(bad) && (tid & 63) == 0) a.cull[0] = raised | 1;
     }
 }
 
@@ -81,7 +82,7 @@ __global__ __launch_bounds__(kGrpThreads) void k_cull_grouped(CullArgs a) {
     __shared__ int s_at[2], s_k[2];
     constexpr int kPer = (kGrpRun + kGrpTail) / kGrpThreads;
     const int tid = threadIdx.x, L = a.n_levels, n = a.n_obs;
-    if (a.cull[0]) {   // (uniform) the general passes start from zeros
+    if (a.cull[0] & 1) {   // (uniform) the general passes start from zeros
         const int64_t nc = (int64_t)a.n_pt * L;
         for (int64_t i = blockIdx.x * (int64_t)kGrpThreads + tid; i < nc; i += (int64_t)gridDim.x * kGrpThreads) a.counters[i] = 0;
         return;
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(kGrpThreads) void k_cull_grouped(CullArgs a) {
 }
 
 __global__ __launch_bounds__(256) void k_cull_count(CullArgs a) {
-    if (!a.cull[0]) return;
+    if (!(a.cull[0] & 1)) return;
     for (int i = blockIdx.x * 256 + threadIdx.x; i < a.n_obs; i += gridDim.x * 256) {
         if (a.active && !a.active[i]) continue;
         const int j = a.pt[i], o = a.oct[i];
@@ -187,7 +188,7 @@ constexpr int kRedRun = 512;      // observations of a block (2048: observations
 __global__ __launch_bounds__(256) void k_cull_redundant(CullArgs a) {
     __shared__ int h_obs[kCullSpan], h_red[kCullSpan];
     __shared__ int wmin[4], wmax[4];
-    if (!a.cull[0]) return;
+    if (!(a.cull[0] & 1)) return;
     const int64_t i0 = (int64_t)blockIdx.x * kRedRun;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     // the block's observations, every load issued before any is used, and their keyframe span
@@ -250,7 +251,7 @@ __global__ __launch_bounds__(256) void k_cull_decide(CullArgs a) {
     const int k = blockIdx.x * 256 + threadIdx.x;
     if (k >= a.n_kf) return;
     const int no = a.kf_obs[k], nr = a.kf_red[k];
-    const bool prot = a.protect && a.protect[k];
+    const bool prot = k == 0 ? a.cull[0] & 2 : a.protect && a.protect[k];
     a.cull[k] = (!prot && no > 0 && (int64_t)a.den * nr >= (int64_t)a.num * no) ? 1 : 0;
 }
 

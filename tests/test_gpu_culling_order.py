@@ -90,3 +90,27 @@ def test_a_late_descent_costs_no_abandoned_pass():
             t.append(time.perf_counter() - t0)
         best.append(min(t))
     assert best[1] <= 1.4 * best[0], best
+
+
+@pytest.mark.parametrize("n_pt, shuffled", [(3000, False), (140000, False), (140000, True)])
+@pytest.mark.parametrize("first", [0, 1])
+def test_protect_and_cull_in_one_array(first, n_pt, shuffled):
+    """A caller's array that holds the protected keyframes and takes the culled ones."""
+    n_kf = 700
+    rng = np.random.default_rng(8)
+    data = _data(rng, np.full(n_pt, 8), n_kf)
+    if shuffled:
+        i = rng.permutation(len(data[0]))
+        data = tuple(d[i] for d in data)
+    protect = (rng.uniform(size=n_kf) < 0.3).astype(np.uint8)
+    protect[0] = first
+    print(f"case culling in place first={first} N={len(data[0])} shuffled={shuffled}", flush=True)
+    apart = lmap.Culling(n_kf, n_pt, *data, LEVELS, protect=protect)
+    apart.run(lmap.cull_params(num=1, den=2), check=False)
+    one = lmap.Culling(n_kf, n_pt, *data, LEVELS, protect=protect)
+    one.cull = one.protect
+    one.run(lmap.cull_params(num=1, den=2), check=False)
+    a, b = apart.result(), one.result()
+    for k in a:
+        np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+    assert a["cull"][0] != first and a["cull"].any()
