@@ -99,6 +99,7 @@ struct Plan {
     int max_n = 0;           // unknowns of the largest reduced system
     size_t lin_lds = 0, upd_lds = 0, chol_lds = 0, init_lds = 0;
     bool chol_hbm = false;   // reduced systems factored in HBM (too large for LDS)
+    bool tiled = false;      // layout of the reduced systems
     int lin_passes = 1;      // linearisation passes over the camera blocks
     int lin_copies = 1;   // copies of the linearisation's camera sums
     int max_En = 0;
@@ -220,7 +221,7 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
     pl.win.resize(nw);
     pl.opt_map.assign(P->n_kf, -1);
     pl.tiles.clear();
-    int64_t part = 0, partr = 0, red = 0, dpo = 0;
+    int64_t part = 0, partr = 0, packed = 0, dpo = 0;
     int maxK = 1, maxn = 0;
     for (int w = 0; w < nw; ++w) {
         WinInfo &W = pl.win[w];
@@ -266,8 +267,7 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
         part += W.part_stride * W.ntiles;
         W.partr_off = partr;
         partr += (int64_t)W.n * W.ntiles;
-        W.red_off = (int32_t)red;
-        red += std::max(red_rhs(W.n, true), W.E) + W.n;   // either layout
+        packed += W.E + W.n;
         W.dp_off = (int32_t)dpo;
         dpo += W.n;
         W.rng0 = 0;
@@ -278,7 +278,15 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
         pl.max_pts = std::max(pl.max_pts, W.M);
         pl.max_kopt = std::max(pl.max_kopt, W.Kopt);
     }
-    if (red > INT32_MAX) return set_error(ctx, LBA_ERR_UNSUPPORTED, "batch too large");
+    if (packed > INT32_MAX) return set_error(ctx, LBA_ERR_UNSUPPORTED, "batch too large");
+    // the layout that the reduced systems are formed in (the joint systems of an inertial solve
+    // are tiled, the visual ones that they take in are not)
+    pl.tiled = !I && maxn <= chol_tile_max_n();
+    int64_t red = 0;
+    for (WinInfo &W : pl.win) {
+        W.red_off = red;
+        red += red_rhs(W.n, pl.tiled) + W.n;
+    }
     // launch the tiles heaviest first (estimated observations times a cost growing with
     // the window's reduced system), so that the light ones fill the end of the launch
     {
@@ -351,6 +359,7 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
     // the inertial measurements: per window their range, the joint reduced system
     pl.vi = I != nullptr;
     int64_t vred = 0, vdp = 0;
+    packed = 0;
     if (pl.vi) {
         if (I->n_edges < 0) return set_error(ctx, LBA_ERR_INVALID_ARGUMENT, "negative n_edges");
         if (I->n_edges > 0 &&
@@ -377,13 +386,14 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
             WinInfo &V = pl.vwin[w];
             V.n = 15 * pl.win[w].Kopt;
             V.E = V.n * (V.n + 1) / 2;
-            V.red_off = (int32_t)vred;
+            V.red_off = vred;
             vred += red_rhs(V.n, true) + V.n;
+            packed += V.E + V.n;
             V.dp_off = (int32_t)vdp;
             vdp += V.n;
             maxn = std::max(maxn, V.n);
         }
-        if (vred > INT32_MAX) return set_error(ctx, LBA_ERR_UNSUPPORTED, "batch too large");
+        if (packed > INT32_MAX) return set_error(ctx, LBA_ERR_UNSUPPORTED, "batch too large");
     }
     // the reduced system is factored in LDS when it fits, else in a per-window copy in HBM
     // (systems of up to chol_tile_max_n() unknowns are factored with the matrix in registers
@@ -899,7 +909,7 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     ra.red = d_red;
     ra.redflag = d_redflag;
     ra.max_En = pl.max_En;
-    ra.tiled = !pl.vi && !pl.chol_hbm;
+    ra.tiled = pl.tiled;
 
     LinSegArgs lsa;
     memset(&lsa, 0, sizeof(lsa));

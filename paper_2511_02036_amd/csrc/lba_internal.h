@@ -24,9 +24,9 @@ struct WinInfo {
     int32_t kf0, K, pt0, M, ob0, N;   // ranges in the concatenated arrays
     int32_t Kopt, n, E;               // optimisable kfs, n = 6 Kopt, E = n (n + 1) / 2
     int32_t tile0, ntiles;            // tiles of this window in the tile list
-    int32_t red_off;                  // doubles: reduced system (E + n) of this window
     int32_t dp_off;                   // doubles: pose step (n) of this window
     int32_t rng0;                     // first of its ranges of positions (segment plan)
+    int64_t red_off;                  // doubles: reduced system of this window (see red_rhs)
     int64_t part_off;                 // doubles: partial S (E per tile) of tile 0
     int64_t part_stride;              // doubles per tile: E
     int64_t partr_off;                // doubles: partial r (n per tile) of tile 0
