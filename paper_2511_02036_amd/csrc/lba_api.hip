@@ -75,6 +75,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr int kSegStageK = 64;     // keyframes whose poses eight wavefronts of a compute unit can stage in LDS
 constexpr int kSegTarget = 4096;   // segments a problem is cut into before they take several chunks
 constexpr int kSegWindow = 900;    // ... and a window
+constexpr double kSegMaxBytes = 32.0 * (1 << 30);   // space of a segment plan and its records
 
 constexpr size_t kGraphCache = 1024;
 
@@ -336,6 +337,16 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
         pl.seg_cap = 5 * chunks / (4 * least) + nr + 64;
         pl.chunk_cap = 2 * chunks + P->n_pt / kSegPoints + 2 * nr + 64;
         pl.rec_cap = (5 * chunks / (4 * third) + nr + 64) * seg_record(std::min(pl.max_kopt, kSegCams));
+        // The workspace is about 215 bytes per observation with plan and records, 60 to 100 in
+        // the general form.  Beyond 32 GiB of them (some 200 million observations) the problem
+        // takes the general form, so that every batch that fits the card with it still does.
+        const double bytes = (double)sizeof(double) * pl.rec_cap +
+                             (double)(sizeof(Seg) + 2 * sizeof(double) + sizeof(int32_t)) * pl.seg_cap +
+                             (double)(sizeof(int4) + sizeof(int32_t)) * pl.chunk_cap + 7.0 * sizeof(double) * P->n_pt;
+        if (bytes > kSegMaxBytes) {
+            pl.ranges.clear();
+            pl.seg_cap = pl.chunk_cap = pl.rec_cap = 0;
+        }
     }
     // LDS: the update block uses four wavefronts if its staging fits, fewer otherwise
     pl.waves = 0;

@@ -42,3 +42,16 @@ def test_batches_up_to_the_limit_of_packed_systems(windows, kopt, precision):
     assert _workspace(windows, kopt, precision=precision) > 8 * windows * n * (n + 1) // 2
     with pytest.raises(lba.LBAError, match="batch too large"):
         _workspace(limit + 1, kopt, precision=precision)
+
+
+@pytest.mark.parametrize("windows, kopt, points, per_point", [(256, 26, 10000, 7), (2560, 26, 10000, 7),
+                                                              (20000, 26, 10000, 7), (20000, 26, 13000, 8),
+                                                              (65000, 20, 4000, 8)])
+def test_batches_up_to_the_largest_index_fit_the_card(windows, kopt, points, per_point):
+    """FP64 batches of up to 2^31 - 1 observations with their inputs in 288 GB."""
+    n_pt = windows * points
+    n = n_pt * per_point
+    b = _workspace(windows, kopt, points, per_point)
+    total = b + 34 * n + 24 * n_pt
+    print(f"case fit observations={n} workspace={b / 1e9:.1f} GB with inputs {total / 1e9:.1f} GB", flush=True)
+    assert total < 288e9
