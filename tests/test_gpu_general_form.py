@@ -130,3 +130,83 @@ def test_order_of_the_segments():
         s, form = _run(w)
         assert form == "segments"
         assert _in_index_order(s) == index_order
+
+
+def _check_forms(data, windows, form, vi=None, repeats=True, **options):
+    """The form, parity, and the same bits from captured step graphs (where no observation is
+    repeated: the general form adds repeated ones in any order)."""
+    s, ran = _run(data, vi=vi, **options)
+    assert ran == form
+    g = _out(s)
+    if vi is None:
+        _parity(data, g, windows)
+    s.ctx.profile(False)
+    for _ in range(2 if repeats else 0):
+        _same(g, _out(s.run()))
+    return s, g
+
+
+def test_general_batch_with_and_without_records():
+    """Points of more than ten optimisable keyframes in one window turn the segments down for all;
+    sorted and unsorted windows, up to 24 optimisable keyframes (one copy of the camera sums per
+    wavefront and no observation repeated: the same bits with chunk records and without)."""
+    ws = [_window(650 + k, k, 300 + 40 * k, (3, 12 if k == 15 else 9)) for k in (3, 10, 15, 24)]
+    assert [_most_seen(w) > 10 for w in ws] == [False, False, True, False]
+    cat = synth.concat(ws)
+    print(f"case general batch N={len(cat['obs_kf'])}", flush=True)
+    _, a = _check_forms(cat, ws, "general", pair_cache=1)
+    _, b = _check_forms(cat, ws, "general", pair_cache=0)
+    _same(a, b)
+
+
+@pytest.mark.parametrize("kopt", [11, 20, 31, 45])
+def test_general_window_with_and_without_records(kopt):
+    """Points seen by up to 16 keyframes; above 30 optimisable ones several passes over the camera
+    blocks and one copy of the camera sums (equal to rounding only)."""
+    w = _window(660 + kopt, kopt, 900, (4, 16))
+    assert _most_seen(w) > 10
+    print(f"case general window kopt={kopt} N={len(w['obs_kf'])}", flush=True)
+    out = []
+    for cache in (1, 0):
+        s, form = _run(w, pair_cache=cache)
+        assert form == "general"
+        out.append(_out(s))
+        _parity(w, out[-1], [w])
+    if kopt <= 30:
+        _same(*out)
+
+
+@pytest.mark.parametrize("kopt", [20, 36, 50])
+def test_plan_over_its_capacities_matches_oracle(kopt):
+    w = _scattered(670 + kopt, kopt, 5000)
+    assert _most_seen(w) <= 10
+    print(f"case general plan kopt={kopt} N={len(w['obs_kf'])}", flush=True)
+    s, form = _run(w)
+    assert form == "general"
+    _parity(w, _out(s), [w])
+
+
+@pytest.mark.parametrize("why", ["repeat", "long"])
+def test_inertial_window_in_the_general_form_matches_oracle(why):
+    w, vi = synth.vi_window(680, K=16, n_fixed=4, M=500, nobs=(4, 16), stereo_p=0.6)
+    if why == "repeat":
+        w, vi = synth.vi_window(681, K=9, n_fixed=4, M=200, nobs=(3, 6), stereo_p=0.6)
+        w = _repeat_one(w)
+    assert (_most_seen(w) > 10) == (why == "long")
+    print(f"case general inertial {why} N={len(w['obs_kf'])}", flush=True)
+    s, g = _check_forms(w, [w], "general", vi=vi, repeats=why == "long")
+    r = lbaref.solve_vi(w, vi)
+    assert_fp64_parity(w, g["T"], g["X"], g["outlier"], g["stats"][0], r)
+    for k, t in (("V", s.v_out), ("BG", s.bg_out), ("BA", s.ba_out)):
+        assert np.all(np.abs(t.cpu().numpy() - r[k]) <= 1e-8 * np.maximum(1.0, np.abs(r[k]))), k
+
+
+@pytest.mark.parametrize("chunks", [1, 2, 3, 4, 5, 16])
+def test_segments_of_several_chunks_match_oracle(chunks):
+    """A segment takes another chunk (about 52 observations) per 900 chunks of a window, up to 16;
+    the update's block takes as many wavefronts, up to four."""
+    w = _window(690 + chunks, 10, int((chunks - 0.5) * 900 * 52 / 9), (8, 10))
+    n = len(w["obs_kf"])
+    assert (n // 52 + 1 + 899) // 900 == chunks
+    print(f"case segments of {chunks} chunks N={n}", flush=True)
+    _check_forms(w, [w], "segments")
