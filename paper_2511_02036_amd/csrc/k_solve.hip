@@ -608,16 +608,20 @@ __global__ __launch_bounds__(kTileThreads) void k_chol_tile(CholArgs a) {
         }
         if (!ok && lane == 0) s_fail = 1;
     };
-    auto update = [&](d4 D, int I, int J) LBA_INLINE {   // D - (L_Jk) (L_Ik)^T
+    // D - (L_Jk) (L_Ik)^T, the 16 products of an entry summed before they are subtracted: with D
+    // as the matrix instructions' accumulator each of them rounds at D's size, and the pose steps'
+    // error against 80 bits was 25 to 45% larger (same time)
+    auto update = [&](d4 D, int I, int J) LBA_INLINE {
         double qj[4], qi[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            qj[v] = -Qp[J][v][lane];
+            qj[v] = Qp[J][v][lane];
             qi[v] = Qp[I][v][lane];
         }
+        d4 P = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int v = 0; v < 4; ++v) D = __builtin_amdgcn_mfma_f64_16x16x4f64(qj[v], qi[v], D, 0, 0, 0);
-        return D;
+        for (int v = 0; v < 4; ++v) P = __builtin_amdgcn_mfma_f64_16x16x4f64(qj[v], qi[v], P, 0, 0, 0);
+        return D - P;
     };
 
     // ---- factorisation and forward solve ----------------------------------------------

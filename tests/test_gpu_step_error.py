@@ -1,0 +1,137 @@
+"""Rounding error of one FP64 step (the first of a solve), against the same step in 80-bit
+arithmetic: no larger, in the geometric mean over a set of windows, than with the reduced
+systems and sums formed as the bounds' comments say, whose means were measured on these windows.
+The reference is plain NumPy, without the solver's arithmetic: dense blocks, adjugate inverses,
+an unblocked Cholesky."""
+import numpy as np
+import pytest
+
+from paper_2511_02036_amd import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2511_02036_amd import lba  # noqa: E402
+
+L = np.longdouble
+TAU = 1e-5
+HUBER2 = (5.991, 7.815)
+
+
+def _solve(S, r):
+    C, y = S.copy(), r.copy()
+    for j in range(len(r)):
+        C[j, j] = np.sqrt(C[j, j])
+        C[j + 1:, j] /= C[j, j]
+        C[j + 1:, j + 1:] -= np.outer(C[j + 1:, j], C[j + 1:, j])
+    for j in range(len(r)):
+        y[j] /= C[j, j]
+        y[j + 1:] -= C[j + 1:, j] * y[j]
+    for j in range(len(r) - 1, -1, -1):
+        y[j] /= C[j, j]
+        y[:j] -= C[j, :j] * y[j]
+    return y
+
+
+def _exp(d):
+    A, E = np.zeros((4, 4), L), np.eye(4, dtype=L)
+    A[:3, :3] = [[0, -d[2], d[1]], [d[2], 0, -d[0]], [-d[1], d[0], 0]]
+    A[:3, 3] = d[3:]
+    P = E
+    for i in range(1, 25):
+        P = P @ A / i
+        E = E + P
+    return E
+
+
+def first_step(w):
+    """Poses and points after the first step at lambda = tau max diag(H), and the start."""
+    fixed, kf, pt = np.asarray(w["fixed"]), w["obs_kf"], w["obs_pt"]
+    K, kopt = len(fixed), int((fixed == 0).sum())
+    opt = np.where(fixed == 0, np.cumsum(fixed == 0) - 1, -1)
+    T, X = np.asarray(w["T_cw"], L).reshape(K, 3, 4), np.asarray(w["X"], L)
+    z, st = np.asarray(w["obs_z"], L), np.asarray(w["obs_type"]).astype(L)
+    fx, fy, cx, cy, bf = [L(v) for v in w["cam"]]
+    is2 = L(1) / np.asarray(w["sigma2"], L)[w["obs_oct"]]
+    d2 = np.where(st > 0, L(HUBER2[1]), L(HUBER2[0]))
+    mul = lambda A, B: (A[:, :, :, None] * B[:, None, :, :]).sum(2)   # noqa: E731
+    tr = lambda A: A.transpose(0, 2, 1)   # noqa: E731
+    Tk = T[kf]
+    Xc = (Tk[:, :, :3] * X[pt][:, None, :]).sum(-1) + Tk[:, :, 3]
+    x, y, iz = Xc[:, 0], Xc[:, 1], 1 / Xc[:, 2]
+    e = np.stack([z[0] - (fx * x * iz + cx), z[1] - (fy * y * iz + cy), (z[2] - (fx * x * iz + cx - bf * iz)) * st], 1)
+    s = (e * e).sum(1) * is2
+    om = (np.where(s > d2, np.sqrt(d2) / np.sqrt(np.maximum(s, L(1e-300))), L(1)) * is2)[:, None, None]
+    D, A = np.zeros((len(kf), 3, 3), L), np.zeros((len(kf), 3, 6), L)
+    D[:, 0, 0], D[:, 0, 2] = fx * iz, -fx * x * iz * iz
+    D[:, 1, 1], D[:, 1, 2] = fy * iz, -fy * y * iz * iz
+    D[:, 2, 0], D[:, 2, 2] = fx * iz * st, -(fx * x - bf) * iz * iz * st
+    A[:, 0, 1], A[:, 0, 2], A[:, 1, 2] = Xc[:, 2], -y, x
+    A[:, 1, 0], A[:, 2, 0], A[:, 2, 1] = -Xc[:, 2], y, -x
+    A[:, 0, 3] = A[:, 1, 4] = A[:, 2, 5] = 1
+    Jp, Jx = mul(D, A), mul(D, Tk[:, :, :3])
+    M, o = len(X), opt[kf] >= 0
+    k = opt[kf][o]
+    Hll, bl = np.zeros((M, 3, 3), L), np.zeros((M, 3), L)
+    Hpp, bp = np.zeros((kopt, 6, 6), L), np.zeros((kopt, 6), L)
+    np.add.at(Hll, pt, om * mul(tr(Jx), Jx))
+    np.add.at(bl, pt, (om * mul(tr(Jx), e[:, :, None]))[:, :, 0])
+    np.add.at(Hpp, k, (om * mul(tr(Jp), Jp))[o])
+    np.add.at(bp, k, (om * mul(tr(Jp), e[:, :, None]))[o][:, :, 0])
+    lam = L(TAU) * max(np.einsum("mii->mi", Hll).max(), np.einsum("kii->ki", Hpp).max())
+    V = Hll + lam * np.eye(3, dtype=L)
+    adj = np.stack([np.cross(V[:, 1], V[:, 2]), np.cross(V[:, 2], V[:, 0]), np.cross(V[:, 0], V[:, 1])], 1)
+    Vi = adj / (V[:, 0] * adj[:, 0]).sum(1)[:, None, None]
+    W = np.zeros((kopt, 6, M, 3), L)
+    W[k, :, pt[o]] = (om * mul(tr(Jp), Jx))[o]
+    Y = (W[..., None] * Vi[None, None]).sum(3).reshape(6 * kopt, 3 * M)
+    W = W.reshape(6 * kopt, 3 * M)
+    S = -(Y @ W.T)
+    for q in range(kopt):
+        S[6 * q:6 * q + 6, 6 * q:6 * q + 6] += Hpp[q]
+    S[np.arange(6 * kopt), np.arange(6 * kopt)] += lam
+    d = _solve(S, bp.reshape(-1) - Y @ bl.reshape(-1))
+    dl = (Vi * (bl - (W.T @ d).reshape(M, 3))[:, None, :]).sum(-1)
+    Tn = T.copy()
+    for q in np.flatnonzero(opt >= 0):
+        Tn[q] = (_exp(d[6 * opt[q]:6 * opt[q] + 6]) @ np.vstack([T[q], [0, 0, 0, 1]]))[:3]
+    return Tn.reshape(K, 12), X + dl, T.reshape(K, 12), X
+
+
+def _step_error(kind, windows, **kw):
+    errs = []
+    for seed in range(windows):
+        w = synth.tiny_window(5000 + seed, **kw)
+        g = lba.solve(w, device="cuda:0", iters_round1=1, iters_round2=0, max_trials=1, tau=TAU)
+        if g["stats"][0]["iters_r1"] != 1:   # (the step was not taken)
+            continue
+        T, X, T0, X0 = first_step(w)
+        rel = lambda a, b, c: float(np.sqrt(((np.asarray(a, L) - b) ** 2).sum() / ((b - c) ** 2).sum()))   # noqa: E731
+        errs.append((rel(g["T"], T, T0), rel(g["X"], X, X0)))
+    assert len(errs) > 0.9 * windows
+    eT, eX = np.exp(np.log(np.array(errs)).mean(axis=0))
+    print(f"case step error {kind} windows={len(errs)} poses={eT:.4g} points={eX:.4g}", flush=True)
+    return eT, eX
+
+
+CASES = {
+    # 22 optimisable keyframes: several panels of the reduced solve
+    "mid": (24, dict(K=26, n_fixed=4, M=500, nobs=(3, 8), stereo_p=0.5)),
+    # points of two to four monocular observations, whose own terms nearly cancel
+    "far": (160, dict(K=12, n_fixed=3, M=200, nobs=(2, 4), stereo_p=0.0)),
+    "small": (240, dict(K=6, n_fixed=2, M=60, nobs=(2, 5), stereo_p=0.5)),
+}
+
+
+def _check(kind, bound):
+    windows, kw = CASES[kind]
+    eT, eX = _step_error(kind, windows, **kw)
+    assert eT <= 1.04 * bound[0] and eX <= 1.04 * bound[1], (eT, eX, bound)
+
+
+def test_reduced_solve_error():
+    """Means with the reduced system in 4 x 4 register tiles, four products summed at a time."""
+    _check("mid", (9.454e-15, 1.030e-14))
