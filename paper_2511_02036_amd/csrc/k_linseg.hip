@@ -13,11 +13,13 @@
 //   2. the point sums, one (point, entry) per lane; each lane then factors its point's
 //      V = Hll + lambda I = L L^T (reciprocal square roots), and the point's first lane
 //      stores the factor for the update;
-//   3. Z_a = W_a L^-T goes to LDS, and the observation's own terms Hpp_a and
+//   3. Z_a = W_a L^-T goes to LDS, and the observation's own terms Hpp_a - Z_a Z_a^T and
 //      r_a = bp_a - Z_a L^-1 bl into FP64 sums per camera (LDS atomics from the lanes of one
 //      wavefront only, which the hardware applies in a fixed order; two copies, by the
 //      point's parity, halve the lanes that meet at one address);
-//   4. S - Z Z^T on the matrix cores: rows are (camera, component), the contraction runs
+//   4. the blocks of two cameras of -Z Z^T on the matrix cores (those of one camera come out
+//      too and are not read: summed apart from Hpp they would round at the size of what
+//      cancels): rows are (camera, component), the contraction runs
 //      over (point, component) with four points per step.  A lane finds its row's
 //      observation of its point through a byte map (a zero row where the camera does not
 //      see the point), so the operands are gathered from LDS and nothing is padded there.
@@ -343,9 +345,18 @@ __global__ __launch_bounds__(kSegThreads) __attribute__((amdgpu_waves_per_eu(2, 
                                     C00, C10, C20, G00,
                                     C01, C11, C21, 0, G11,
                                     C02, C12, C22, G02, G12, G22};
+                // less Z_a Z_a^T, before either is summed: the two nearly cancel where a point has
+                // few observations (pose steps' error 5 to 10% larger otherwise; same time)
+                double zz[18];
 #pragma unroll
-                for (int i = 0; i < 21; ++i)
-                    if (i != 13) lds_add(dst + i, H[i]);   // (entry (4, 3) is zero)
+                for (int i = 0; i < 18; ++i) zz[i] = sm.Z[lane * ZS + i];
+#pragma unroll
+                for (int i = 0; i < 6; ++i)
+#pragma unroll
+                    for (int j = 0; j <= i; ++j) {
+                        const int e = i * (i + 1) / 2 + j;
+                        lds_add(dst + e, H[e] - (zz[3 * i] * zz[3 * j] + zz[3 * i + 1] * zz[3 * j + 1] + zz[3 * i + 2] * zz[3 * j + 2]));
+                    }
             }
             wave_sync();   // (the next chunk overwrites the staging)
         }
@@ -458,7 +469,7 @@ __global__ __launch_bounds__(64 * kRedSegWaves) void k_reduce_seg(ReduceSegArgs 
                 // (read by every lane: l may have no entry)
                 const double *const vb = a.rec + uniform(ro), *const hb = a.rec + uniform(ho);
                 const int ln = __builtin_amdgcn_readlane(len, l);
-                if (entry) v[u] = vb[i * ln + j];
+                if (entry && !diag) v[u] = vb[i * ln + j];
                 if (diag && (entry || rside)) h[u] = hb[hoff];
             }
 #pragma unroll

@@ -184,7 +184,8 @@ struct Seg {
 };
 
 // row tiles of a segment over u cameras, and the doubles of its record: the 6 x 6 blocks of
-// the lower block triangle, then per camera Hpp (21, lower) and r (6)
+// the lower block triangle (those of one camera unused), then per camera the sums of its
+// observations' own terms Hpp_a - Z_a Z_a^T (21, lower) and r_a (6)
 __host__ __device__ inline int seg_blocks(int u) { return 36 * (u * (u + 1) / 2); }
 __host__ __device__ inline int seg_record(int u) { return seg_blocks(u) + 27 * u; }
 
