@@ -98,7 +98,6 @@ __global__ __launch_bounds__(kSegThreads) __attribute__((amdgpu_waves_per_eu(2, 
     if (lane < kMaxLevels + 2) wt[lane] = lane < kMaxLevels ? a.c.inv_sigma2[lane] : a.c.huber2[lane - kMaxLevels];
     wave_sync();
     SegLds &sm = *reinterpret_cast<SegLds *>(smem + sizeof(double) * (kMaxLevels + 2));
-    double *const Tl = reinterpret_cast<double *>(smem + sizeof(double) * (kMaxLevels + 2) + sizeof(SegLds));   // poses
     const int nseg = a.info[kSegInfoCount];
     const ZT *const sz = static_cast<const ZT *>(a.sz);
     const CamParams cam = a.c.cam;
@@ -128,8 +127,6 @@ __global__ __launch_bounds__(kSegThreads) __attribute__((amdgpu_waves_per_eu(2, 
         };
         int4 ck = S.first;
         load_obs(ck);
-        if (a.stage_k > 0)
-            for (int i = lane; i < 12 * S.K; i += 64) Tl[i] = Tw[i];
         if (!running) continue;
         const double *Xs = state ? a.X1 : a.X0;
         auto load_points = [&](const int4 &k) {
@@ -173,13 +170,10 @@ __global__ __launch_bounds__(kSegThreads) __attribute__((amdgpu_waves_per_eu(2, 
             double bp[6];
             {
                 double T[12];
-                if (a.stage_k > 0) {
+                // (from memory: staged in LDS once per segment they cost 1 to 2% of a solve with up to
+                // 40 keyframes, and 6% from 48 on, where only seven segments fit a compute unit)
 #pragma unroll
-                    for (int i = 0; i < 12; ++i) T[i] = Tl[12 * kf + i];
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 12; ++i) T[i] = Tw[12 * kf + i];
-                }
+                for (int i = 0; i < 12; ++i) T[i] = Tw[12 * kf + i];
                 double xc, yc, zc, eu, ev, er;
                 const double e2 = residual(cam, T, sm.xs[3 * pl], sm.xs[3 * pl + 1], sm.xs[3 * pl + 2], (double)z0,
                                            (double)z1, (double)z2, stereo, xc, yc, zc, eu, ev, er);
@@ -391,7 +385,7 @@ __global__ __launch_bounds__(kSegThreads) __attribute__((amdgpu_waves_per_eu(2, 
 
 hipError_t launch_linseg(const LinSegArgs &a, int64_t seg_cap, bool z_f32, hipStream_t s) {
     if (seg_cap <= 0) return hipSuccess;
-    const size_t lds = sizeof(double) * (kMaxLevels + 2) + sizeof(SegLds) + sizeof(double) * 12 * a.stage_k;
+    const size_t lds = sizeof(double) * (kMaxLevels + 2) + sizeof(SegLds);
     const dim3 grid((unsigned)std::min<int64_t>(seg_cap, 1 << 16)), block(kSegThreads);   // (a stride beyond)
     if (z_f32) hipLaunchKernelGGL(k_linseg<float>, grid, block, lds, s, a);
     else hipLaunchKernelGGL(k_linseg<double>, grid, block, lds, s, a);

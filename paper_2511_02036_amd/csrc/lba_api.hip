@@ -72,7 +72,6 @@ lba_status set_error(lba_ctx *ctx, lba_status st, const char *fmt, ...) {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-constexpr int kSegStageK = 64;     // keyframes whose poses eight wavefronts of a compute unit can stage in LDS
 constexpr int kSegTarget = 4096;   // segments a problem is cut into before they take several chunks
 constexpr int kSegWindow = 900;    // ... and a window
 constexpr double kSegMaxBytes = 32.0 * (1 << 30);   // space of a segment plan and its records
@@ -940,7 +939,6 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     lsa.info = d_err;
     lsa.n_obs = P->n_obs;
     lsa.n_pt = P->n_pt;
-    lsa.stage_k = pl.max_k <= kSegStageK ? pl.max_k : 0;
     lsa.c = c;
 
     UpdSegArgs usa;

@@ -223,7 +223,6 @@ struct LinSegArgs {
     int32_t *segfail;            // per segment: a point block did not factorise
     const int32_t *info;
     int32_t n_obs, n_pt, robust;
-    int32_t stage_k;            // poses a wavefront stages in LDS (0: read from memory)
     SolveConsts c;
 };
 
