@@ -91,7 +91,11 @@ typedef struct {
                                 complement (which observations of a point pair up on which
                                 camera block) in the workspace for the rest of an LM round, so
                                 that only the first step of a round forms it; 0: formed at
-                                every step.  The results are the same [1] */
+                                every step.  The results are the same [1].  Only where pairs
+                                are listed: in mixed precision, and in FP64 for problems with a
+                                point seen by more than ten optimisable keyframes, a repeated
+                                (point, keyframe) or points seen by very different keyframes;
+                                other FP64 problems are linearised by segments of points */
 } lba_options;
 
 typedef struct {
@@ -267,7 +271,10 @@ lba_status lba_solve_inertial(lba_ctx *ctx, const lba_problem *problem, const lb
 /* Tile tuner of the batched form.  The linearisation kernel runs one block per tile of
  * a window's points (the update one block per part of a tile); the tile size trades
  * per-tile work (the partial reduced system each tile writes and the fixed-order sum over
- * tiles) against the number of blocks that fill the GPU.  lba_tune times short solves
+ * tiles) against the number of blocks that fill the GPU.  (FP64 problems that are linearised
+ * by segments, see pair_cache, use the tiles for the damping initialisation alone, and are
+ * timed as such; measured on four such problems, the table was the one that the same
+ * problem tunes to with its pairs listed.)  lba_tune times short solves
  * (three LM steps on every window, on `stream`; the least of three runs after a first
  * that captures the step graph) of this problem with candidate tile sizes 64 ... 4096
  * points, one value per class of windows (LBA_TUNE_CLASSES classes: optimisable
@@ -295,7 +302,7 @@ lba_status lba_tune_set(lba_ctx *ctx, const int32_t *points_per_tile);
 typedef enum {
     LBA_KCLASS_LINEARIZE = 0,    /* residual + Jacobian + Hessian blocks + Schur, per step */
     LBA_KCLASS_LINEARIZE_INIT,   /* cost and damping scale at the start of a round */
-    LBA_KCLASS_REDUCE,           /* fixed-order sum of the per-tile partial systems */
+    LBA_KCLASS_REDUCE,           /* fixed-order sum of the partial systems of tiles or segments */
     LBA_KCLASS_CHOLESKY,         /* FP64 factorisation and solve of the reduced system */
     LBA_KCLASS_UPDATE,           /* back-substitution, retraction and trial cost */
     LBA_KCLASS_DECIDE,           /* gain ratio, accept / reject, damping update */
@@ -306,7 +313,9 @@ typedef enum {
     LBA_KCLASS_FINALIZE,
     LBA_KCLASS_COST_FORWARD,     /* robust-cost layer, forward */
     LBA_KCLASS_COST_BACKWARD,    /* robust-cost layer, backward */
-    LBA_KCLASS_ORDER,            /* once per solve: point order of the linearisation */
+    LBA_KCLASS_ORDER,            /* once per solve: point order of the linearisation, the segment
+                                    plan (FP64), and where pairs are listed the observations
+                                    copied into that order: three launches in FP64, two else */
     LBA_KCLASS_INERTIAL,         /* inertial measurements: residuals, blocks, joint system */
     LBA_KCLASS_COUNT
 } lba_kernel_class;

@@ -60,19 +60,14 @@ struct SegLds {
 };
 
 // 3 x 3 Cholesky V = L L^T and Li = L^-1 by reciprocal square roots (order as chol3_inv)
-__device__ __forceinline__ double rsqrt_step(double p) {
-    const double y = __builtin_amdgcn_rsq(p);
-    const double e = fma(-(p * y), y, 1.0);
-    return fma(y * e, fma(e, 0.375, 0.5), y);
-}
 __device__ __forceinline__ bool chol3_rsqrt(const double *V /*00 01 02 11 12 22*/, double *Li) {
-    const double i00 = rsqrt_step(V[0]);
+    const double i00 = rsqrt_fp64(V[0]);
     const double l10 = V[1] * i00, l20 = V[2] * i00;
     const double d1 = V[3] - l10 * l10;
-    const double i11 = rsqrt_step(d1);
+    const double i11 = rsqrt_fp64(d1);
     const double l21 = (V[4] - l20 * l10) * i11;
     const double d2 = V[5] - l20 * l20 - l21 * l21;
-    const double i22 = rsqrt_step(d2);
+    const double i22 = rsqrt_fp64(d2);
     const double i10 = -l10 * i00 * i11;
     Li[0] = i00; Li[1] = i10; Li[2] = i11;
     Li[3] = -(l20 * i00 + l21 * i10) * i22;

@@ -258,7 +258,7 @@ hipError_t launch_seg_plan(const SegPlanArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// the outlier flags of round 2 into the words (and out of them: a.mask null)
+// the outlier flags of round 2 into the words
 __global__ __launch_bounds__(256) void k_seg_mask(SegPlanArgs a) {
     const int lane = threadIdx.x & 63;
     const int64_t nwv = (int64_t)gridDim.x * (blockDim.x / 64);

@@ -448,13 +448,6 @@ __device__ __forceinline__ double row_bcast(double v) {
     return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(v), 0x150 + j, 0xF, 0xF, true));
 }
 
-// reciprocal square root: the hardware estimate and one third-order step
-__device__ __forceinline__ double rsqrt_fp64(double p) {
-    const double y = __builtin_amdgcn_rsq(p);
-    const double e = fma(-(p * y), y, 1.0);
-    return fma(y * e, fma(e, 0.375, 0.5), y);
-}
-
 // elimination steps j .. 15 with a row per lane of the tile (A) and of what becomes the
 // transposed inverse factor (B); columns from `real` on are padding (pivot 1)
 template <int j>

@@ -309,13 +309,18 @@ lba_status build_plan(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, Pl
     // Segment form, for FP64 solves (the mixed form's FP32 sums depend on how the general
     // form groups the products: on slowly converging windows another grouping moves points
     // by 1e-7 to 1e-6 of the map's extent, about as far as that form is from FP64).
-    // A chunk holds at most 64 observations (about 52 in the mean).  A segment's record is 16
+    // A chunk holds at most 64 observations (about 52 in the mean).  A segment's record is 18
     // KB, written once and read once, so fewer and longer segments save traffic; but about
     // 2048 wavefronts are resident, and segments of uneven length leave the last of them
     // alone.  Measured, linearisation + reduction + update per step: 48 windows of 1.4
     // million observations 380 us with at most 32 chunks per segment, 245 with 13, 223 with
-    // 7, 230 with 5; one window of 64,000 observations 48 us with one, 37 with two.  A range of positions holds about
-    // four segments (the last one of a range is cut short).
+    // 7, 230 with 5; one window of 64,000 observations 48 us with one, 37 with two.  Whole
+    // solves, with kSegTarget halved, as it is and doubled: 48 windows of 30 keyframes 7.03,
+    // 6.64 and 7.02 ms, 48 of 5 to 40 6.44, 5.95 and 6.25, 16 windows 3.41, 3.43 and 3.55, 256
+    // the same (16 chunks).  With kSegWindow 450, 600, 900 and 1,400: one window of 43,000
+    // observations 1.48, 1.50, 1.52 and 1.52 ms, 61,000 1.54, 1.51, 1.49 and 1.61, 134,000
+    // 2.30, 2.23, 2.16 and 2.16, 190,000 3.32, 3.08, 2.89 and 3.48.  A range of positions
+    // holds about four segments (the last one of a range is cut short).
     if (!pl.mixed && P->n_obs > 0 && P->n_pt <= kSegMaxPoints) {
         const int64_t chunks = P->n_obs / 52 + 1;
         pl.seg_chunks = (int)std::min<int64_t>(kSegMaxChunks, std::max((chunks + kSegTarget - 1) / kSegTarget,
@@ -923,7 +928,6 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
 
     LinSegArgs lsa;
     memset(&lsa, 0, sizeof(lsa));
-    lsa.win = d_win;
     lsa.segs = sa.segs;
     lsa.chunks = sa.chunks;
     lsa.pinfo = d_pinfo;
@@ -977,7 +981,9 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     rsa.tiled = ra.tiled;
     rsa.range_pts = pl.range_pts;
     rsa.max_kopt = pl.max_kopt;
-    // about 16 segments per wavefront of a camera block
+    // about 16 segments per wavefront of a camera block (8, 16 and 32: solves of 48 windows 6.97,
+    // 6.64 and 6.69 ms, 16 windows 3.44, 3.43 and 3.31, one of 61,000 observations 1.495, 1.493
+    // and 1.499)
     rsa.waves = (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, P->n_obs / 52 / std::min(pl.seg_chunks, 16) / nw / 16));
 
     CholArgs ca;

@@ -183,7 +183,7 @@ struct Seg {
     int4 first;                // its first chunk
 };
 
-// row tiles of a segment over u cameras, and the doubles of its record: the 6 x 6 blocks of
+// doubles of the record of a segment over u cameras: the 6 x 6 blocks of
 // the lower block triangle (those of one camera unused), then per camera the sums of its
 // observations' own terms Hpp_a - Z_a Z_a^T (21, lower) and r_a (6)
 __host__ __device__ inline int seg_blocks(int u) { return 36 * (u * (u + 1) / 2); }
@@ -201,7 +201,7 @@ struct SegPlanArgs {
     Seg *segs;
     int4 *chunks;                // first position, points, first place, observations | cameras << 8
     int32_t *chunk_seg;          // segment of each chunk
-    uint32_t *words;             // per place (see k_seg_emit)
+    uint32_t *words;             // per place (see k_seg_gather)
     void *sz;                    // measurements by place, the type of obs.z
     int32_t *info;
     int64_t seg_cap, chunk_cap, rec_cap;
@@ -209,7 +209,6 @@ struct SegPlanArgs {
 };
 
 struct LinSegArgs {
-    const WinInfo *win;
     const Seg *segs;
     const int4 *chunks;
     const int4 *pinfo;
@@ -615,6 +614,13 @@ __device__ __forceinline__ double residual(const CamParams &cam, const double *T
     ev = zv - v;
     er = stereo ? zr - (u - cam.bf * iz) : 0.0;
     return eu * eu + ev * ev + er * er;
+}
+
+// reciprocal square root: the hardware estimate and one third-order step
+__device__ __forceinline__ double rsqrt_fp64(double p) {
+    const double y = __builtin_amdgcn_rsq(p);
+    const double e = fma(-(p * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
 // 3x3 SPD Cholesky V = L L^T and the inverse factor Li = L^-1 (both lower, 6 entries in
