@@ -41,9 +41,10 @@ constexpr int kGrpOrderBlocks = 4096;
 
 // Whether the single pass can take the observations.  Reads the point indices only, run by
 // run, and stops once any block has raised the flag.  Deciding this within the single pass wasted
-// the pass where a descent came late: 5 million observations of 2,000 random keyframes 1,219 us
-// so, 743 now, 738 in general passes alone; bound by reading the indices (18 us of 310 at 28
-// million in order).
+// the pass where a descent came late: 18 million observations of 2.6 million points 576 us so,
+// 390 now, 398 in general passes alone.  Bound by reading the indices: 14.7 us of 210 for those
+// in order (5 TB/s; with every index before another loaded rather than taken from the lane below,
+// 20.7 us).
 __global__ __launch_bounds__(kGrpThreads) void k_cull_order(CullArgs a) {
     const int tid = threadIdx.x, n = a.n_obs;
     const int64_t most = (int64_t)kGrpTiles * (kGrpCounts / a.n_levels);   // points of a run
@@ -52,17 +53,21 @@ __global__ __launch_bounds__(kGrpThreads) void k_cull_order(CullArgs a) {
         const int last = n - 1;
         const int first = a.pt[max((int)r0 - 1, 0)], final = a.pt[min((int64_t)last, r0 + kGrpRun - 1)],
                   tail = a.pt[min((int64_t)last, r0 + kGrpRun + kGrpTail - 1)];
-        int pt[kGrpRun / kGrpThreads], before[kGrpRun / kGrpThreads];
+        int pt[kGrpRun / kGrpThreads], edge[kGrpRun / kGrpThreads];
+        const int w0 = (tid & ~63) - 1;   // before the wavefront's first
 #pragma unroll
         for (int u = 0; u < kGrpRun / kGrpThreads; ++u) {   // (past the end: the last one again)
-            const int i = (int)min((int64_t)last, r0 + tid + u * kGrpThreads);
-            pt[u] = a.pt[i];
-            before[u] = a.pt[max(i - 1, 0)];
+            pt[u] = a.pt[(int)min((int64_t)last, r0 + tid + u * kGrpThreads)];
+            edge[u] = a.pt[max(0, (int)min((int64_t)last, r0 + __builtin_amdgcn_readfirstlane(w0) + u * kGrpThreads))];
         }
         if (raised & 1) return;
         bool bad = false;
 #pragma unroll
-        for (int u = 0; u < kGrpRun / kGrpThreads; ++u) bad = bad || pt[u] < 0 || pt[u] >= a.n_pt || before[u] > pt[u];
+        for (int u = 0; u < kGrpRun / kGrpThreads; ++u) {
+            int before = __shfl_up(pt[u], 1, 64);
+            if ((tid & 63) == 0) before = edge[u];
+            bad = bad || pt[u] < 0 || pt[u] >= a.n_pt || before > pt[u];
+        }
         // the run's points, and its last point's tail
         const bool end = r0 + kGrpRun >= n;
         const int64_t p0 = r0 == 0 ? 0 : (int64_t)first + 1, p1 = end ? a.n_pt : (int64_t)final + 1;
@@ -72,7 +77,7 @@ __global__ __launch_bounds__(kGrpThreads) void k_cull_order(CullArgs a) {
 }
 
 // Bound by the latency of a run's loads, LDS counts and sums, one after the other, with four
-// blocks per compute unit: 18 million observations of 2.6 million points take 180 us (1.5 TB/s
+// blocks per compute unit: 18 million observations of 2.6 million points take 160 us (1.7 TB/s
 // of its bytes), the zeroing and two passes before it 376.  More LDS for the counts, shorter
 // runs, or registers for six blocks per unit cost 10 to 60% more; four copies of the totals,
 // by lane, are 2% faster than one.  With the flag raised the launch zeroes the counters instead.
@@ -183,20 +188,24 @@ __global__ __launch_bounds__(256) void k_cull_count(CullArgs a) {
 }
 
 constexpr int kCullSpan = 1024;   // keyframes per block summed in LDS
-constexpr int kRedRun = 512;      // observations of a block (2048: observations by keyframe 6% slower)
+// Two observations per thread: more, or a loop over runs, lose the order in which neighbouring
+// blocks meet the same points (28 million observations by keyframe: 1,816 us, four per thread
+// 1,970, eight 2,040, two runs per block 1,900); 512 threads rather than 256 halve the blocks
+// that return at once where the single pass ran.
+constexpr int kRedThreads = 512, kRedRun = 2 * kRedThreads;   // observations of a block
 
-__global__ __launch_bounds__(256) void k_cull_redundant(CullArgs a) {
+__global__ __launch_bounds__(kRedThreads) void k_cull_redundant(CullArgs a) {
     __shared__ int h_obs[kCullSpan], h_red[kCullSpan];
-    __shared__ int wmin[4], wmax[4];
+    __shared__ int wmin[kRedThreads / 64], wmax[kRedThreads / 64];
     if (!(a.cull[0] & 1)) return;
     const int64_t i0 = (int64_t)blockIdx.x * kRedRun;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     // the block's observations, every load issued before any is used, and their keyframe span
-    constexpr int kPer = kRedRun / 256;
+    constexpr int kPer = kRedRun / kRedThreads;
     int kf[kPer], pt[kPer], oc[kPer], on[kPer];
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
-        const int64_t i = min(i0 + threadIdx.x + 256 * u, (int64_t)a.n_obs - 1);   // (past the end: the last one again)
+        const int64_t i = min(i0 + threadIdx.x + kRedThreads * u, (int64_t)a.n_obs - 1);   // (past the end: the last one again)
         kf[u] = a.kf[i];
         pt[u] = a.pt[i];
         oc[u] = a.oct[i];
@@ -216,16 +225,19 @@ __global__ __launch_bounds__(256) void k_cull_redundant(CullArgs a) {
         wmin[wv] = kmin;
         wmax[wv] = kmax;
     }
-    for (int k = threadIdx.x; k < kCullSpan; k += 256) h_obs[k] = h_red[k] = 0;
+    for (int k = threadIdx.x; k < kCullSpan; k += kRedThreads) h_obs[k] = h_red[k] = 0;
     __syncthreads();
-    kmin = min(min(wmin[0], wmin[1]), min(wmin[2], wmin[3]));
-    kmax = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+#pragma unroll
+    for (int w = 0; w < kRedThreads / 64; ++w) {
+        kmin = min(kmin, wmin[w]);
+        kmax = max(kmax, wmax[w]);
+    }
     const bool local = kmax >= kmin && kmax - kmin < kCullSpan;
     const int L = a.n_levels;
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
         const int k = kf[u], j = pt[u], o = oc[u];
-        if (i0 + threadIdx.x + 256 * u >= a.n_obs || !on[u] || k < 0 || k >= a.n_kf || j < 0 || j >= a.n_pt || o >= L) continue;
+        if (i0 + threadIdx.x + kRedThreads * u >= a.n_obs || !on[u] || k < 0 || k >= a.n_kf || j < 0 || j >= a.n_pt || o >= L) continue;
         const int top = min(L - 1, o + a.slack);
         const int32_t *c = a.counters + (size_t)j * L;
         int others = -1;   // the observation itself is one of the counted
@@ -241,7 +253,7 @@ __global__ __launch_bounds__(256) void k_cull_redundant(CullArgs a) {
     }
     if (!local) return;
     __syncthreads();
-    for (int k = threadIdx.x; k <= kmax - kmin; k += 256) {
+    for (int k = threadIdx.x; k <= kmax - kmin; k += kRedThreads) {
         if (h_obs[k]) atomicAdd(&a.kf_obs[kmin + k], h_obs[k]);
         if (h_red[k]) atomicAdd(&a.kf_red[kmin + k], h_red[k]);
     }
@@ -286,12 +298,12 @@ void launch_cull(const CullArgs &a, hipStream_t s) {
             hipLaunchKernelGGL(k_cull_grouped, dim3(std::max(runs, zero)), dim3(kGrpThreads), 0, s, a);
             prof_end(s);
         }
-        const unsigned blocks = (unsigned)std::min(8192, (a.n_obs + 255) / 256);
+        const unsigned blocks = (unsigned)std::min(4096, (a.n_obs + 255) / 256);
         prof_begin(LMAP_KCLASS_CULL_COUNT, s);
         hipLaunchKernelGGL(k_cull_count, dim3(blocks), dim3(256), 0, s, a);
         prof_end(s);
         prof_begin(LMAP_KCLASS_CULL_REDUNDANT, s);
-        hipLaunchKernelGGL(k_cull_redundant, dim3((unsigned)(((int64_t)a.n_obs + kRedRun - 1) / kRedRun)), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_cull_redundant, dim3((unsigned)(((int64_t)a.n_obs + kRedRun - 1) / kRedRun)), dim3(kRedThreads), 0, s, a);
         prof_end(s);
     }
     prof_begin(LMAP_KCLASS_CULL_DECIDE, s);
