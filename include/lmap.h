@@ -233,7 +233,8 @@ typedef enum {
     LMAP_KCLASS_CORR_SEARCH,      /* correspondence search (matrix cores + validation) */
     LMAP_KCLASS_CORR_RESOLVE,     /* deferred resolution of the correspondence search */
     LMAP_KCLASS_FUSE,             /* fusion candidate search */
-    LMAP_KCLASS_CULL_COUNT,       /* per-point per-octave counters */
+    LMAP_KCLASS_CULL_COUNT,       /* per-point per-octave counters; where observations are grouped
+                                     by point (2^20 or more) the redundancy test with them */
     LMAP_KCLASS_CULL_REDUNDANT,   /* redundancy test and per-keyframe totals */
     LMAP_KCLASS_CULL_DECIDE,      /* per-keyframe decision */
     LMAP_KCLASS_CHECK,            /* input validation */

@@ -287,19 +287,19 @@ void launch_cull(const CullArgs &a, hipStream_t s) {
     // end of the last run's tail
     const int64_t nc = (int64_t)a.n_pt * a.n_levels;
     const bool grouped = a.n_obs >= kGrpMinObs && a.n_obs <= INT32_MAX - kGrpRun - kGrpTail;
+    prof_begin(LMAP_KCLASS_PREP, s);
     hipLaunchKernelGGL(k_cull_begin, dim3((a.n_kf + 255) / 256), dim3(256), 0, s, a, grouped ? 0 : 1);
+    prof_end(s);
     if (!grouped) launch_fill_i32(a.counters, nc, 0, s);
     if (a.n_obs > 0) {
+        prof_begin(LMAP_KCLASS_CULL_COUNT, s);
         if (grouped) {
             const int runs = (a.n_obs + kGrpRun - 1) / kGrpRun;
-            prof_begin(LMAP_KCLASS_CULL_COUNT, s);
             hipLaunchKernelGGL(k_cull_order, dim3(std::min(runs, kGrpOrderBlocks)), dim3(kGrpThreads), 0, s, a);
             const int zero = (int)std::min<int64_t>(4096, (nc + 1023) / 1024);
             hipLaunchKernelGGL(k_cull_grouped, dim3(std::max(runs, zero)), dim3(kGrpThreads), 0, s, a);
-            prof_end(s);
         }
         const unsigned blocks = (unsigned)std::min(4096, (a.n_obs + 255) / 256);
-        prof_begin(LMAP_KCLASS_CULL_COUNT, s);
         hipLaunchKernelGGL(k_cull_count, dim3(blocks), dim3(256), 0, s, a);
         prof_end(s);
         prof_begin(LMAP_KCLASS_CULL_REDUNDANT, s);

@@ -114,3 +114,17 @@ def test_protect_and_cull_in_one_array(first, n_pt, shuffled):
     for k in a:
         np.testing.assert_array_equal(a[k], b[k], err_msg=k)
     assert a["cull"][0] != first and a["cull"].any()
+
+
+@pytest.mark.parametrize("n_pt", [2000, 140000])
+def test_counting_is_one_launch_of_its_class_per_call(n_pt):
+    """The benchmark divides a call's bytes by the class's mean: a call whose counting takes
+    several kernels counts once."""
+    job = lmap.Culling(300, n_pt, *_data(np.random.default_rng(2), np.full(n_pt, 8), 300), LEVELS)
+    lmap.profile(True)
+    for _ in range(3):
+        job.run(check=False)
+    prof = lmap.profile_read()
+    lmap.profile(False)
+    print(f"case culling profile N={8 * n_pt} {prof['cull_count']}", flush=True)
+    assert [prof[k][0] for k in ("cull_count", "cull_redundant", "cull_decide")] == [3, 3, 3]
