@@ -1075,7 +1075,7 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     if (use_seg) {
         // the points live by position; the kernels that walk them in index order (damping
         // initialisation, flags, output) read a copy brought up to date before each use
-        HIPCHK(launch_to_positions(d_pinfo, d_X0, usa.X0, P->n_pt, s));
+        HIPCHK(timed(ctx, LBA_KCLASS_SETUP, s, [&] { return launch_to_positions(d_pinfo, d_X0, usa.X0, P->n_pt, s); }));
         la.X1 = d_X0;
         m.X1 = d_X0;
     }
@@ -1086,9 +1086,9 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         if (round == 2) {
             m.count = 0;
             oa.mask = R->outlier;
-            if (use_seg) HIPCHK(launch_from_positions(usa, d_X0, nw, pl.max_pts, s));
             HIPCHK(timed(ctx, LBA_KCLASS_FLAGS, s, [&] {
-                hipError_t e = launch_flags(m, nw, pl.max_obs, s);
+                hipError_t e = use_seg ? launch_from_positions(usa, d_X0, nw, pl.max_pts, s) : hipSuccess;
+                if (e == hipSuccess) e = launch_flags(m, nw, pl.max_obs, s);
                 if (e != hipSuccess) return e;
                 sa.mask = R->outlier;
                 return use_seg ? launch_seg_mask(sa, s) : launch_order_gather(oa, true, s);   // the flags in places
@@ -1183,8 +1183,10 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         }
     }
     m.count = 1;
-    if (use_seg) HIPCHK(launch_from_positions(usa, d_X0, nw, pl.max_pts, s));
-    HIPCHK(timed(ctx, LBA_KCLASS_FLAGS, s, [&] { return launch_flags(m, nw, pl.max_obs, s); }));
+    HIPCHK(timed(ctx, LBA_KCLASS_FLAGS, s, [&] {
+        hipError_t e = use_seg ? launch_from_positions(usa, d_X0, nw, pl.max_pts, s) : hipSuccess;
+        return e != hipSuccess ? e : launch_flags(m, nw, pl.max_obs, s);
+    }));
     HIPCHK(timed(ctx, LBA_KCLASS_FINALIZE, s, [&] { return launch_finalize(m, nw, s); }));
     if (pl.vi) HIPCHK(timed(ctx, LBA_KCLASS_FINALIZE, s, [&] { return launch_vi_finish(va, s); }));
     if (R->log && pl.log_cap > 0)

@@ -142,6 +142,16 @@ def _check_forms(data, windows, form, vi=None, repeats=True, **options):
     return s, g
 
 
+@pytest.mark.parametrize("nobs, setups", [((3, 8), 2), ((12, 14), 1)])
+def test_every_kernel_of_a_solve_is_in_a_class(nobs, setups):
+    """The segments' copy of the points by position is timed with the set-up (its way back with the
+    flags)."""
+    s, form = _run(_window(645, 12, 300, nobs))
+    print(f"case classes {form}", flush=True)
+    assert (form == "segments") == (setups == 2)
+    assert s.ctx.profile_read()["setup"][0] == setups
+
+
 def test_general_batch_with_and_without_records():
     """Points of more than ten optimisable keyframes in one window turn the segments down for all;
     sorted and unsorted windows, up to 24 optimisable keyframes (one copy of the camera sums per
