@@ -31,8 +31,9 @@
 // work and LDS round trips, and the waits for the next chunk's data, at two wavefronts per
 // SIMD (the sums of four row tiles take 80 registers); a small problem is bound by the chain
 // of one chunk, about 20k cycles.  Per step, against k_linearize (one block per tile of
-// points, pairs of observations listed and summed by the vector units): 12 us for one window
-// of 12,000 observations (35), 20 us for 64,000 (45), 133 us for 48 windows of 1.4 million together (362).
+// points, pairs of observations listed and summed by the vector units): 11.4 us for one window
+// of 12,000 observations (35), 19.4 us for 64,000 (45), 131 us for 48 windows of 1.4 million
+// together (362).
 // One segment per workgroup: four to a workgroup waited for the longest of them (half as
 // slow again on batches).
 #include "lba_internal.h"
@@ -391,7 +392,7 @@ hipError_t launch_linseg(const LinSegArgs &a, int64_t seg_cap, bool z_f32, hipSt
 // records -> reduced system.  One block per camera block (kA <= kB) of one window: its
 // wavefronts share the window's segments and add up those that hold both cameras (lanes: the
 // 36 entries, for a diagonal block the 21 lower ones and the 6 of r), and their sums are
-// combined in a fixed order.  Bound by the records' bytes on batches (46 us for 48
+// combined in a fixed order.  Bound by the records' bytes on batches (41 us for 48
 // windows of 1.4 million observations, k_reduce took 10 for its partial systems), by the chain of loads on one
 // window (10 us at 64,000 observations); eight loads in flight, more cost occupancy (16:
 // half as slow again on large batches).
