@@ -74,6 +74,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 constexpr int kSegTarget = 4096;   // segments a problem is cut into before they take several chunks
 constexpr int kSegWindow = 900;    // ... and a window
+constexpr int kSegOneStep = 1 << 18;   // observations from which one LM step earns the segment plan
 constexpr double kSegMaxBytes = 32.0 * (1 << 30);   // space of a segment plan and its records
 
 constexpr size_t kGraphCache = 1024;
@@ -816,6 +817,12 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     // point order of the linearisation (the observation structure is fixed for the solve),
     // and the observations copied into it
     int4 *d_pinfo = static_cast<int4 *>(W_(pl.o_pinfo));
+    // Without a step the segment plan is for nothing, and one step earns it on large problems only
+    // (12,000 observations 208 us with it and 224 without, 61,000 339 and 269, 190,000 549 and 562,
+    // 2.7 million 2,083 and 2,973; two and one iterations of 61,000: 520 and 595).  The workspace
+    // has room for it either way: its size does not depend on the iterations.
+    const int64_t steps = (int64_t)opt.iters_round1 + opt.iters_round2;
+    bool use_seg = !pl.ranges.empty() && (steps >= 2 || (steps == 1 && P->n_obs >= kSegOneStep));
     ObsView sob = ob;
     sob.pt = nullptr;
     sob.kf = static_cast<const int32_t *>(W_(pl.o_skf));
@@ -833,7 +840,7 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
         oa.kfmask = static_cast<unsigned long long *>(W_(pl.o_kfmask));
         oa.tmp = static_cast<int32_t *>(W_(pl.o_ptmp));
         oa.pinfo = d_pinfo;
-        oa.max_cams = pl.ranges.empty() ? 0 : kSegCams;
+        oa.max_cams = use_seg ? kSegCams : 0;
         oa.by_keyframes = 1;
         oa.n_pt = P->n_pt;
         oa.obs = ob;
@@ -869,7 +876,6 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     sa.max_chunks = pl.seg_chunks;
     sa.max_cams = kSegCams;
     const bool acc32 = pl.mixed && opt.schur_fp32_accum;
-    bool use_seg = !pl.ranges.empty();
     if (use_seg) HIPCHK(timed(ctx, LBA_KCLASS_ORDER, s, [&] { return launch_seg_plan(sa, s); }));
     HIPCHK(hipMemcpyAsync(down, d_err, sizeof(int32_t) * 4, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
@@ -877,10 +883,11 @@ lba_status solve_impl(lba_ctx *ctx, const lba_problem *P, const lba_batch *B, lb
     memcpy(info, down, sizeof(info));
     HIPCHK(collect_timing(ctx));
     if (info[0]) return set_error(ctx, LBA_ERR_INVALID_ARGUMENT, "invalid input: %s", describe_input_error(info[0]).c_str());
+    const bool planned = use_seg;
     if (info[kSegInfoGeneral]) use_seg = false;
     if (!use_seg)
         HIPCHK(timed(ctx, LBA_KCLASS_ORDER, s, [&] {
-            hipError_t e = info[kSegInfoGeneral] == kSegOver ? launch_order_general(oa, nw, pl.max_pts, s) : hipSuccess;
+            hipError_t e = planned && info[kSegInfoGeneral] == kSegOver ? launch_order_general(oa, nw, pl.max_pts, s) : hipSuccess;
             return e != hipSuccess ? e : launch_order_gather(oa, false, s);
         }));
 

@@ -216,3 +216,22 @@ def test_segments_of_several_chunks_match_oracle(chunks):
     assert (n // 52 + 1 + 899) // 900 == chunks
     print(f"case segments of {chunks} chunks N={n}", flush=True)
     _check_forms(w, [w], "segments")
+
+
+def test_segments_are_planned_for_two_steps_or_more():
+    """A solve of at most one step lists its pairs; the workspace has one size for all."""
+    w = _window(646, 12, 400, (3, 8))
+    sizes, launches = set(), []
+    for iters in ((0, 0), (1, 0), (0, 1), (1, 1), (2, 0)):
+        print(f"case steps {iters}", flush=True)
+        ctx = lba.Context(0, iters_round1=iters[0], iters_round2=iters[1])
+        s = lba.Solver(ctx, lba.DeviceProblem(w, device=DEV))
+        sizes.add(s.ws_bytes)
+        ctx.profile(True)
+        g = _out(s.run())
+        prof = ctx.profile_read()
+        launches.append((prof["order"][0], prof["setup"][0]))
+        assert_fp64_parity(w, g["T"], g["X"], g["outlier"], g["stats"][0],
+                           lbaref.solve(w, iters_round1=iters[0], iters_round2=iters[1]))
+    assert len(sizes) == 1
+    assert launches == [(2, 1)] * 3 + [(2, 2)] * 2   # (order and copy, or order and plan with the points' copy)
