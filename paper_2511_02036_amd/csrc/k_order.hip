@@ -24,11 +24,16 @@
 //                 position: the point, its first observation, its observation count and the
 //                 place of the first observation in the observation order that follows the
 //                 points' order.
-// The result is deterministic.  k_order_gather (general linearisation) or k_seg_gather then
-// copies the observations into that order (once per solve), and the outlier flags go there
-// once per round, so that the linearisation reads each chunk's observations as one
-// contiguous range.  One block per window with rounds of 1024 ranked points took 163 us for
-// one window of 20,000 points.
+//   k_order_window  the same order by one 1024-thread block per window.
+// A block per lowest keyframe reads a window's keys once each, which pays while the card has
+// room for the blocks.  Whole calls without a step, us, a block per lowest keyframe and per
+// window: 30 optimisable keyframes, 20,000 points: one window 273 and 348, 8 windows 358 and 435,
+// 32 windows 751 and 693, 128 windows 2,458 and 1,832; 22 keyframes, 8,000 points: 209 and 208,
+// 270 and 273, 409 and 359, 1,022 and 778; 3,000 points: 182 and 166, 191 and 180, 304 and 254.
+// The result is deterministic, and the same either way.  k_order_gather (general linearisation)
+// or k_seg_gather then copies the observations into that order (once per solve), and the outlier
+// flags go there once per round, so that the linearisation reads each chunk's observations as
+// one contiguous range.
 #include "lba_internal.h"
 
 #include <algorithm>
@@ -38,7 +43,9 @@ namespace lba {
 constexpr int kOrdThreads = 1024;
 constexpr int kOrdWaves = kOrdThreads / kWave;
 constexpr int kBuckets = 64;             // digit range: optimisable keyframe index, Kopt = none
-
+constexpr int kOrdLdsPoints = 49152;     // windows up to this many points sort from LDS digits
+// a block per lowest keyframe for so many windows at most, if one has so many points
+constexpr int kOrdSplitWindows = 8, kOrdSplitPoints = 8000;
 constexpr int kSortMinKopt = 20;         // the general form sorts windows with more optimisable keyframes
 
 __device__ __forceinline__ bool sorted_window(const OrderArgs &a, const WinInfo &W) {
@@ -61,6 +68,7 @@ __global__ __launch_bounds__(256) void k_order_identity(OrderArgs a) {
 __global__ __launch_bounds__(256) void k_order_keys(OrderArgs a) {
     if (*a.err) return;
     const WinInfo W = a.win[blockIdx.y];
+    if (a.max_cams == 0 && !sorted_window(a, W)) return;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < W.M; i += gridDim.x * blockDim.x) {
         const int P = W.pt0 + i;
         const int o0 = a.pt_start[P], o1 = a.pt_start[P + 1];
@@ -173,6 +181,114 @@ __global__ __launch_bounds__(kOrdThreads) void k_order(OrderArgs a) {
     }
 }
 
+// The same order by one block per window, for batches: two stable counting-sort passes over Kopt + 1
+// buckets (by the highest keyframe, then by the lowest), each ranking a round of 1024 points with
+// one ballot per bucket per wavefront, from digits staged in LDS where they fit.  The second pass
+// writes each position's record without its place; a last scan adds that.
+//
+// One pass: element i of the input order is src[i] (window-local; the identity without src), its
+// bucket the 6-bit digit of its key at bit sh.  It goes to place pos of the output: dst[pos], or in
+// the last pass pinfo[pos].
+template <bool kLast, typename Key>
+__device__ void order_pass(const OrderArgs &a, const WinInfo &W, const Key *key, const int32_t *src, int32_t *dst, int sh,
+                           int *base, int *wcnt) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, M = W.M;
+    const int nb = W.Kopt + 1;
+    if (tid < kBuckets) base[tid] = 0;
+    __syncthreads();
+    for (int i = tid; i < M; i += kOrdThreads) atomicAdd(&base[(key[src ? src[i] : i] >> sh) & (kBuckets - 1)], 1);
+    __syncthreads();
+    if (tid == 0) {
+        int s = 0;
+        for (int b = 0; b < nb; ++b) {
+            const int c = base[b];
+            base[b] = s;
+            s += c;
+        }
+    }
+    __syncthreads();
+    for (int r = 0; r < M; r += kOrdThreads) {
+        const int i = r + tid;
+        const bool valid = i < M;
+        const int e = valid ? (src ? src[i] : i) : -1;
+        const int d = valid ? (int)(key[e] >> sh) & (kBuckets - 1) : -1;
+        int ps = 0, pe = 0;
+        if (kLast && valid) {   // in flight during the ranking
+            ps = a.pt_start[W.pt0 + e];
+            pe = a.pt_start[W.pt0 + e + 1];
+        }
+        int rank = 0, mine = 0;
+        for (int b = 0; b < nb; ++b) {
+            const unsigned long long bal = __ballot(d == b);
+            if (d == b) rank = __popcll(bal & ((1ull << lane) - 1ull));
+            if (lane == b) mine = __popcll(bal);
+        }
+        wcnt[wave * kBuckets + lane] = mine;
+        __syncthreads();
+        if (valid) {
+            int pos = base[d] + rank;
+            for (int w = 0; w < wave; ++w) pos += wcnt[w * kBuckets + d];
+            if (kLast) a.pinfo[W.pt0 + pos] = make_int4(W.pt0 + e, ps, pe - ps, 0);
+            else dst[pos] = e;
+        }
+        __syncthreads();
+        if (tid < kBuckets) {
+            int s = 0;
+            for (int w = 0; w < kOrdWaves; ++w) s += wcnt[w * kBuckets + tid];
+            base[tid] += s;
+        }
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(kOrdThreads) void k_order_window(OrderArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int base[kBuckets];
+    __shared__ int wcnt[kOrdWaves * kBuckets];
+    if (*a.err) return;
+    const WinInfo W = a.win[blockIdx.x];
+    if (!sorted_window(a, W)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t *key = a.keys + W.pt0;
+    int32_t *tmp = a.tmp + W.pt0;
+    if (W.M <= kOrdLdsPoints) {
+        uint16_t *lk = reinterpret_cast<uint16_t *>(smem);
+        for (int i = tid; i < W.M; i += kOrdThreads) lk[i] = (uint16_t)(key[i] & 0xfffu);
+        __syncthreads();
+        order_pass<false>(a, W, lk, nullptr, tmp, 6, base, wcnt);   // by the highest keyframe
+        __syncthreads();
+        order_pass<true>(a, W, lk, tmp, nullptr, 0, base, wcnt);    // then, stably, by the lowest
+    } else {
+        order_pass<false>(a, W, key, nullptr, tmp, 6, base, wcnt);
+        __syncthreads();
+        order_pass<true>(a, W, key, tmp, nullptr, 0, base, wcnt);
+    }
+    __syncthreads();
+    // places: the window's first observation plus the exclusive prefix of the counts in this order
+    int carry = W.ob0;
+    for (int r = 0; r < W.M; r += kOrdThreads) {
+        const int i = r + tid;
+        const int m = i < W.M ? a.pinfo[W.pt0 + i].z : 0;
+        int x = m;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) wcnt[wave] = x;
+        __syncthreads();
+        int add = carry, tot = 0;
+        for (int w = 0; w < kOrdWaves; ++w) {
+            const int v = wcnt[w];
+            add += w < wave ? v : 0;
+            tot += v;
+        }
+        if (i < W.M) a.pinfo[W.pt0 + i].w = add + x - m;
+        carry += tot;
+        __syncthreads();
+    }
+}
+
 // Each wavefront takes 64 consecutive positions of the order; their places form one
 // contiguous range (a point's observations follow the previous position's, across
 // windows too).  The lanes walk that range 64 places at a time (coalesced writes); each
@@ -238,8 +354,12 @@ hipError_t launch_order(const OrderArgs &a, int n_windows, int max_points, int m
     const bool sort = a.by_keyframes && max_kopt > (a.max_cams > 0 ? a.max_cams : kSortMinKopt);
     if (sort || a.max_cams > 0) hipLaunchKernelGGL(k_order_keys, dim3(bx, n_windows), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_order_identity, dim3(bx, n_windows), dim3(256), 0, s, a);
-    if (sort)
+    if (sort && n_windows <= kOrdSplitWindows && max_points >= kOrdSplitPoints) {
         hipLaunchKernelGGL(k_order, dim3(max_kopt + 1, n_windows), dim3(kOrdThreads), 0, s, a);
+    } else if (sort) {
+        const size_t lds = sizeof(uint16_t) * (size_t)std::min(max_points, kOrdLdsPoints);
+        hipLaunchKernelGGL(k_order_window, dim3(n_windows), dim3(kOrdThreads), lds, s, a);
+    }
     return hipGetLastError();
 }
 

@@ -235,3 +235,35 @@ def test_segments_are_planned_for_two_steps_or_more():
                            lbaref.solve(w, iters_round1=iters[0], iters_round2=iters[1]))
     assert len(sizes) == 1
     assert launches == [(2, 1)] * 3 + [(2, 2)] * 2   # (order and copy, or order and plan with the points' copy)
+
+
+def _expected_order(w):
+    """Points by lowest, then highest optimisable keyframe (none last), ties by index."""
+    opt = np.where(np.asarray(w["fixed"]) == 0, np.cumsum(np.asarray(w["fixed"]) == 0) - 1, -1)
+    k = opt[w["obs_kf"]]
+    M, none = len(w["X"]), int((opt >= 0).sum())
+    lo, hi = np.full(M, none), np.full(M, -1)
+    np.minimum.at(lo, w["obs_pt"][k >= 0], k[k >= 0])
+    np.maximum.at(hi, w["obs_pt"][k >= 0], k[k >= 0])
+    hi[lo == none] = none
+    return np.lexsort((np.arange(M), hi, lo))
+
+
+@pytest.mark.parametrize("windows, M", [(1, 7999), (1, 8000), (8, 8000), (9, 8000), (1, 49152), (1, 49153), (2, 1025)])
+def test_both_sorts_give_the_order(windows, M):
+    """A block per lowest keyframe (up to 8 windows, one of 8000 points or more), or one block per
+    window (digits in LDS up to 49,152 points)."""
+    ws = [_window(700 + i, 22, M if i == 0 else 60 + i, (2, 4)) for i in range(windows)]
+    cat = synth.concat(ws)
+    print(f"case sort windows={windows} M={M}", flush=True)
+    ctx = lba.Context(0, iters_round1=0, iters_round2=0, precision="mixed")
+    s = lba.Solver(ctx, lba.DeviceProblem(cat, device=DEV)).run()
+    rec, p0, o0 = [], 0, 0
+    for w in ws:
+        order = _expected_order(w)
+        n = np.bincount(w["obs_pt"], minlength=len(w["X"]))
+        first = np.concatenate([[0], np.cumsum(n)])[:-1]
+        place = np.concatenate([[0], np.cumsum(n[order])])[:-1]
+        rec.append(np.stack([p0 + order, o0 + first[order], n[order], o0 + place], axis=1))
+        p0, o0 = p0 + len(w["X"]), o0 + len(w["obs_kf"])
+    assert np.concatenate(rec).astype(np.int32).tobytes() in s.ws.cpu().numpy().tobytes()
