@@ -29,7 +29,8 @@
 // room for the blocks.  Whole calls without a step, us, a block per lowest keyframe and per
 // window: 30 optimisable keyframes, 20,000 points: one window 273 and 348, 8 windows 358 and 435,
 // 32 windows 751 and 693, 128 windows 2,458 and 1,832; 22 keyframes, 8,000 points: 209 and 208,
-// 270 and 273, 409 and 359, 1,022 and 778; 3,000 points: 182 and 166, 191 and 180, 304 and 254.
+// 270 and 273, 409 and 359, 1,022 and 778; 3,000 points: 182 and 166, 191 and 180, 304 and 254;
+// the sort alone, 42 keyframes, 4,000 points: one window 49 and 65, 96 windows 202 and 105.
 // The result is deterministic, and the same either way.  k_order_gather (general linearisation)
 // or k_seg_gather then copies the observations into that order (once per solve), and the outlier
 // flags go there once per round, so that the linearisation reads each chunk's observations as
@@ -44,8 +45,10 @@ constexpr int kOrdThreads = 1024;
 constexpr int kOrdWaves = kOrdThreads / kWave;
 constexpr int kBuckets = 64;             // digit range: optimisable keyframe index, Kopt = none
 constexpr int kOrdLdsPoints = 49152;     // windows up to this many points sort from LDS digits
-// a block per lowest keyframe for so many windows at most, if one has so many points
-constexpr int kOrdSplitWindows = 8, kOrdSplitPoints = 8000;
+// a block per lowest keyframe for so many windows at most, if points x optimisable keyframes of
+// the largest come to so much
+constexpr int kOrdSplitWindows = 8;
+constexpr int64_t kOrdSplitWork = 160000;
 constexpr int kSortMinKopt = 20;         // the general form sorts windows with more optimisable keyframes
 
 __device__ __forceinline__ bool sorted_window(const OrderArgs &a, const WinInfo &W) {
@@ -354,7 +357,7 @@ hipError_t launch_order(const OrderArgs &a, int n_windows, int max_points, int m
     const bool sort = a.by_keyframes && max_kopt > (a.max_cams > 0 ? a.max_cams : kSortMinKopt);
     if (sort || a.max_cams > 0) hipLaunchKernelGGL(k_order_keys, dim3(bx, n_windows), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_order_identity, dim3(bx, n_windows), dim3(256), 0, s, a);
-    if (sort && n_windows <= kOrdSplitWindows && max_points >= kOrdSplitPoints) {
+    if (sort && n_windows <= kOrdSplitWindows && (int64_t)max_points * max_kopt >= kOrdSplitWork) {
         hipLaunchKernelGGL(k_order, dim3(max_kopt + 1, n_windows), dim3(kOrdThreads), 0, s, a);
     } else if (sort) {
         const size_t lds = sizeof(uint16_t) * (size_t)std::min(max_points, kOrdLdsPoints);
